@@ -18,7 +18,7 @@ namespace gdp {
 static_assert(kPoolRows == kMeanpoolRows, "mean-pool chunk size");
 static_assert(kAttnQ == kAttnBlockQ, "attention query block");
 static_assert(kSampleRows == kSampleChunk, "sampling chunk");
-static_assert(kEvalRows == kEvalChunk, "evaluator memory chunk");
+static_assert(kEvalWindowRows == kEvalWindow, "evaluator window");
 
 // ---------------------------------------------------------------------------
 // Event timer (diagnostics): an event pair around every launch of a selected
@@ -829,9 +829,8 @@ extern "C" int gdp_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_sam
                                                  at<int>(ws, pl.scan_tmp), st));
   GDP_LAUNCH(GDP_K_EVALUATE, launch_fill_reverse(g->row_ptr, g->col_idx, in_ptr, N, g->n_edges, counters + N, in_idx,
                                                  st));
-  const GraphTable gt = make_table(g);
-  GraphTable ct = make_table(g);
-  const int chunks = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalRows, ct.blk);
+  GraphTable wt = make_table(g);
+  const int windows = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalWindowRows, wt.blk);
   EvalLaunch L;
   L.placements = placements;
   L.op_cost = op_cost;
@@ -841,16 +840,17 @@ extern "C" int gdp_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_sam
   L.in_ptr = in_ptr;
   L.in_idx = in_idx;
   L.n_edges = g->n_edges;
-  L.gt = &gt;
-  L.chunk_table = &ct;
-  L.chunks = chunks;
+  L.window_table = &wt;
+  L.windows = windows;
   L.n = N;
   L.D = n_devices;
   L.K = k_samples;
   L.time_unit = time_unit;
+  L.hdr = at<void>(ws, pl.hdr);
+  L.win = at<void>(ws, pl.win);
   L.rec = at<void>(ws, pl.rec);
-  L.memsum = at<void>(ws, pl.memsum);
   L.far = at<unsigned>(ws, pl.far);
+  L.far_stride = pl.far_stride;
   L.makespan = makespan;
   L.valid = valid;
   L.run_time = run_time;

@@ -240,19 +240,26 @@ void plan_place(const gdp_graph* g, const gdp_placer* pl, PlacePlan* p) {
 }
 
 void plan_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k, EvalPlan* p) {
+  (void)n_devices;
   const size_t N = (size_t)g->n_nodes, E = (size_t)g->n_edges;
-  const size_t kb = ((size_t)k + 63) / 64;
   int32_t blk[GDP_MAX_GRAPHS + 1];
-  p->chunks = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalRows, blk);
+  p->windows = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalWindowRows, blk);
+  int longest = 0;
+  for (int i = 0; i < g->n_graphs; ++i) {
+    const int n = g->graph_ptr_h[i + 1] - g->graph_ptr_h[i];
+    if (n > longest) longest = n;
+  }
+  p->far_stride = (N + 63) / 64 * 64;
   carve_init(&p->c);
   p->counters = carve_add(&p->c, (2 * N + 1) * 4);
   p->scan_tmp = carve_add(&p->c, 2 * ((N + 1023) / 1024) * 4);
   p->in_ptr = carve_add(&p->c, (N + 1) * 4);
   p->s_ptr = carve_add(&p->c, (N + 1) * 4);
   p->in_idx = carve_add(&p->c, (E > 0 ? E : 1) * 4);
+  p->hdr = carve_add(&p->c, N * 16);
+  p->win = carve_add(&p->c, (size_t)p->windows * 16);
   p->rec = carve_add(&p->c, (E > 0 ? E : 1) * 8);
-  p->memsum = carve_add(&p->c, (size_t)g->n_graphs * (size_t)k * (size_t)n_devices * 8);
-  p->far = carve_add(&p->c, kb * N * 64 * 4);
+  p->far = carve_add(&p->c, longest > kEvalMinRing ? (size_t)k * p->far_stride * 4 : 0);
 }
 
 int check_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p) {

@@ -71,8 +71,9 @@ struct SamplePlan {
 struct EvalPlan {
   Carve c;
   size_t counters;    // [in_deg: N | cursor: N | spare: 1]
-  size_t scan_tmp, in_ptr, s_ptr, in_idx, rec, memsum, far;
-  int chunks;
+  size_t scan_tmp, in_ptr, s_ptr, in_idx, hdr, win, rec, far;
+  size_t far_stride;  // words per sample of the finish times kept in memory
+  int windows;
 };
 void plan_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_samples, EvalPlan* p);
 
@@ -107,6 +108,7 @@ constexpr int kAttnQ = 128;         // queries per attention work-group
 // post-attention work-group per compute unit.
 constexpr int kSplitRows = 256 * 128;
 constexpr int kSampleRows = 256;    // nodes per sampling work-group
-constexpr int kEvalRows = 256;      // nodes per device-memory work-group of the evaluator
+constexpr int kEvalWindowRows = 64;  // nodes per window of the evaluator
+constexpr int kEvalMinRing = 4096;   // graphs up to this length never need their finish times in memory
 
 }  // namespace gdp

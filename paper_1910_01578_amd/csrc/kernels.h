@@ -237,19 +237,22 @@ struct EvalLaunch {
   const int* in_ptr;           // [n + 1]
   const int* in_idx;           // [n_edges]
   int64_t n_edges;
-  const GraphTable* gt;        // graphs (ptr)
-  const GraphTable* chunk_table;   // graphs and their 256-node chunks (blk)
-  int chunks;
+  const GraphTable* window_table;  // graphs and their kEvalWindow-node windows (blk)
+  int windows;
   int n, D, K;
   double time_unit;
+  void* hdr;                   // scratch: n int4
+  void* win;                   // scratch: windows int4
   void* rec;                   // scratch: n_edges int2
-  void* memsum;                // scratch: G * K * D uint64
-  unsigned* far;               // scratch: ceil(K / 64) * n * 64 uint32
+  unsigned* far;               // scratch: K * far_stride uint32 when a graph is longer than eval_ring()
+  size_t far_stride;           // >= n, a multiple of 64
   int64_t* makespan;           // [G, K]
   unsigned char* valid;        // [G, K]
   float* run_time;             // [G, K] or null
 };
-constexpr int kEvalChunk = 256;
+constexpr int kEvalWindow = 64;
+// Nodes whose finish times stay on chip for G graphs and K samples.
+int eval_ring(const int32_t* graph_ptr, int G, int K);
 hipError_t launch_evaluate(const EvalLaunch& L, hipStream_t s);
 
 }  // namespace gdp

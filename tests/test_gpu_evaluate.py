@@ -140,3 +140,49 @@ def test_evaluate_feeds_advantages():
     ref = O.rewards_advantages(rt.cpu().numpy(), valid.cpu().numpy(), np.zeros(g.n_graphs), np.zeros(g.n_graphs, np.int64))
     np.testing.assert_allclose(reward.cpu().numpy(), ref["reward"], rtol=1e-6, atol=1e-6)
     np.testing.assert_allclose(adv.cpu().numpy(), ref["advantage"], rtol=0, atol=1e-5)
+
+
+def _dag(n, rng, dense, far, far_span):
+    """A DAG of n ops: every op reads its predecessor; inside every second run of
+    64 ops each op reads every dense-th op of the 100 before it, and `far` ops
+    read one op at least far_span ids back."""
+    src, dst = [np.arange(n - 1)], [np.arange(1, n)]
+    for v in range(1, n):
+        if dense and (v // 64) % 2:
+            u = np.arange(max(0, v - 100), v - 1, dense)
+            src.append(u)
+            dst.append(np.full(u.size, v))
+    if far:
+        v = rng.integers(far_span + 1, n, far)
+        u = (rng.random(far) * (v - far_span)).astype(np.int64)
+        src.append(u)
+        dst.append(v)
+    key = np.unique(np.concatenate(src) * np.int64(n) + np.concatenate(dst))
+    s, d = key // n, key % n
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(s, minlength=n))])
+    return row_ptr, d
+
+
+@pytest.mark.parametrize("n,K,D,dense,far,far_span", [
+    (200, 3, 5, 1, 0, 0),            # up to 99 predecessors, beyond the slots, in and before the window
+    (1000, 2, 64, 7, 50, 300),       # some beyond the slots, old ones among them
+    (33000, 2, 8, 0, 3000, 32700),   # 32,768 finish times on chip: read-backs at their edge
+    (17000, 260, 3, 0, 900, 16300),  # 16,384 on chip
+    (8300, 515, 2, 0, 900, 8100),    # 8,192
+    (4200, 1030, 8, 0, 900, 4000),   # 4,096
+])
+def test_evaluate_windows_and_rings(n, K, D, dense, far, far_span):
+    """Edges beyond the per-op slots, and every length of the on-chip ring of
+    finish times with predecessors on both sides of its edge."""
+    from paper_1910_01578_amd import gdp
+    base = W.get_config("tiny_layered_256")
+    rng = np.random.default_rng(n)
+    row_ptr, col = _dag(n, rng, dense, far, far_span)
+    g = W.graph_from_arrays(base, [0, n], row_ptr, col, W.make_features(base, n, rng))
+    cap = np.array([100 * n // D], np.int64)
+    costs = W.OpCosts(rng.integers(0, 50, n).astype(np.int32), rng.integers(0, 90, n).astype(np.int32),
+                      rng.integers(1, 200, n).astype(np.int32), cap)
+    skew = rng.random((K, 1))
+    pl = np.where(rng.random((K, n)) < skew, rng.integers(0, D, (K, 1)), rng.integers(0, D, (K, n))).astype(np.int32)
+    _check(g, costs, pl, D, gdp.Evaluator(gdp.DeviceGraph(g, base.dtype), D, K, costs))
+    _log("evaluate windows", n, K, "ok")
