@@ -16,20 +16,22 @@
 // over the edges inside the window until no lane changes.  The graph is
 // acyclic, so the fixed point is the schedule, exact in integers.  Plain edges
 // need as many repeats as the longest chain has edges (up to 64); edges that
-// skip 2, 4 and 8 ops along a device's chain and along each op's latest
+// skip 2 to 16 ops along a device's chain and 2 to 8 along each op's latest
 // predecessor, formed by pointer doubling, cut that to about 5 - 11.
 //
-// Two waves share the work: wave 1 forms window w + 1's edge lists (static
-// ones from the records below, the skips, and the arrival times from nodes
-// finished before window w) while wave 0 solves window w.  Finish times of the
-// last R nodes stay in LDS; older ones of graphs longer than R nodes are read
-// back from a global copy.  What bounds it is wave 0's chain of LDS lane
-// permutes.  One sample at 52,000 nodes on 8 devices takes what 64 take, as
-// every sample has its own compute unit.
+// Four waves share the work: while wave 0 solves window w, wave 1 forms window
+// w + 2's edge lists, wave 3 its device chains and wave 2 the arrival times at
+// window w + 1 from nodes before window w.  Finish times of the last R nodes stay in
+// LDS; older ones of graphs longer than R nodes are read back from a global
+// copy.  What bounds it is wave 0's chain of LDS
+// round trips: about 280 cycles a repeat and 7 - 10 repeats plus 900 cycles a
+// window.  52,000 ops, 64 samples: 1.01 ms (op by op on one wave: 30.4 ms);
+// 2,500 ops, 16 samples: 77 us (933 us).
 //
 // Times below 2^26 units (they share a word with the device or a lane number),
 // saturating; a graph with a finish time of 2^26 or more gets the result -1.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -42,6 +44,11 @@ constexpr int kWin = 64;                        // nodes per window, one per lan
 constexpr unsigned kTimeLimit = 1u << 26;
 constexpr int kSlots = 4;                       // edges per node and kind held as lane pointers
 constexpr unsigned kNone = 0xffu;               // an unused slot
+// A chain of this many latest predecessors inside a window makes its skip edges
+// worth their permutes: layered graphs stay below it (their repeats do not fall
+// with the skips), operator chains are far above (48 -> 11 repeats at 2,500 ops).
+constexpr int kDeep = 10;
+constexpr int kDeepBit = 64;
 
 static_assert(kWin == kEvalWindow, "evaluator window");
 
@@ -49,7 +56,7 @@ static_assert(kWin == kEvalWindow, "evaluator window");
 //   node header  {cost, out_xfer, internal slots, near slots}: four bytes each,
 //                the lane of a predecessor in the node's own window (slot 0 the
 //                latest) and in the window before it
-//   window       {first record, old records, first extra record, extra records << 6 | slots in use}
+//   window       {first record, old records, first extra record, extra records << 7 | deep << 6 | slots in use}
 //   records of a window's in-edges: the old ones (predecessors before the
 //                previous window) from the front, the extra ones (beyond the
 //                slots) from the back; {u relative to the graph | big << 31,
@@ -67,7 +74,7 @@ __global__ __launch_bounds__(256) void k_window_lists(const int* __restrict__ in
                                                       int2* __restrict__ rec) {
   __shared__ int ptr[kWin + 1], best[kWin], cin[kWin], cnear[kWin];
   __shared__ unsigned char slot_in[kWin][kSlots], slot_near[kWin][kSlots];
-  __shared__ int n_old, n_extra, m_in, m_near;
+  __shared__ int n_old, n_extra, m_in, m_near, deep;
   const int w = blockIdx.x, t = threadIdx.x;
   const int g = graph_of_block(wt, w);
   const int g0 = wt.ptr[g], v0 = g0 + (w - wt.blk[g]) * kWin;
@@ -77,7 +84,7 @@ __global__ __launch_bounds__(256) void k_window_lists(const int* __restrict__ in
     best[t] = cin[t] = cnear[t] = 0;
     for (int q = 0; q < kSlots; ++q) slot_in[t][q] = slot_near[t][q] = (unsigned char)kNone;
   }
-  if (t == 0) n_old = n_extra = m_in = m_near = 0;
+  if (t == 0) n_old = n_extra = m_in = m_near = deep = 0;
   __syncthreads();
   const int rb = ptr[0], re = ptr[cnt];
   auto lane_of = [&](int e) {                   // largest lane with ptr[lane] <= e
@@ -115,10 +122,16 @@ __global__ __launch_bounds__(256) void k_window_lists(const int* __restrict__ in
     atomicMax(&m_in, best[t] > 0 ? min(1 + cin[t], kSlots) : 0);
     atomicMax(&m_near, min(cnear[t], kSlots));
     auto bytes = [](const unsigned char* b) { return (int)(b[0] | b[1] << 8 | b[2] << 16 | (unsigned)b[3] << 24); };
+    int u = t, steps = 0;                       // steps back along the latest predecessors
+    while (steps < kDeep && best[u] > 0) {
+      u = best[u] - 1;
+      ++steps;
+    }
+    if (steps == kDeep) deep = 1;
     hdr[v0 + t] = make_int4(op_cost[v0 + t], out_xfer[v0 + t], bytes(slot_in[t]), bytes(slot_near[t]));
   }
   __syncthreads();
-  if (t == 0) win[w] = make_int4(rb, n_old, re - n_extra, n_extra << 6 | m_near << 3 | m_in);
+  if (t == 0) win[w] = make_int4(rb, n_old, re - n_extra, n_extra << 7 | (deep ? kDeepBit : 0) | m_near << 3 | m_in);
 }
 
 struct EvalArgs {
@@ -158,32 +171,42 @@ __device__ __forceinline__ unsigned lane_at(unsigned v, unsigned sel) {
   return (unsigned)__builtin_amdgcn_ds_bpermute((int)(sel << 2), (int)v);
 }
 
-// What wave 1 hands wave 0 for one window, per lane; an edge is weight << 6 |
-// lane of its source (weights include the cost of the node itself, but for the
-// near edges).  An absent edge is the lane itself with weight 0.
+// One window's edge lists per lane; an edge is weight << 6 | lane of its source
+// (weights include the cost of the node itself, but for the near edges).  An
+// absent edge is the lane itself with weight 0.
+struct Lists {
+  uint4 in;                // edges from the node's own window
+  uint4 near;              // edges from the window before (~0: none)
+  uint4 chain;             // 1, 2, 4 and 8 ops back on the node's device
+  uint4 skip;              // 2, 4 and 8 steps back along the latest predecessors; cost << 6 | device
+  unsigned chain16;        // 16 ops back on the device
+  uint4 w;                 // the same in every lane: slots in use, first and last extra record, 0
+  uint2 last;              // the same in every lane: the lanes that are the last of their device
+};
 struct WinBuf {
-  uint4 in[kWin];          // edges from the node's own window
-  uint4 near[kWin];        // edges from the window before (~0: none)
-  uint4 chain[kWin];       // 1, 2, 4 and 8 ops back on the node's device
-  uint4 skip[kWin];        // 2, 4 and 8 steps back along the latest predecessors; cost << 6 | device
-  unsigned ready[kWin];    // latest arrival from older nodes
-  unsigned last_lo, last_hi;   // lanes that are the last of their device
-  int slots, extra0, extra1;   // slots in use; the extra records
+  uint4 in[kWin], near[kWin], chain[kWin], skip[kWin];
+  unsigned chain16[kWin];
+  uint4 w;
+  uint2 last;
 };
 
 constexpr int kMemSpread = 8;    // copies of the per-device memory sums (fewer lanes on one address)
 
 template <int R>
-__global__ __launch_bounds__(128) void k_list_schedule(EvalArgs a, GraphTable wt, CapTable caps) {
+__global__ __launch_bounds__(256) void k_list_schedule(EvalArgs a, GraphTable wt, CapTable caps) {
   __shared__ unsigned ring[R];                  // packed (finish, device) of the last R nodes
   __shared__ __attribute__((aligned(16))) WinBuf buf[2];
+  __shared__ unsigned ready[2][kWin];           // latest arrivals from old nodes
+  __shared__ unsigned flds[kWin];               // finish times during the repeats
   __shared__ unsigned fbuf[2 * kWin];           // finish times of this window and the one before (extra records)
   __shared__ unsigned arr[kWin];
   __shared__ unsigned dev_free[GDP_MAX_DEVICES];
   __shared__ unsigned long long mem[GDP_MAX_DEVICES][kMemSpread];
   __shared__ int side_wrapped;
   const int lane = threadIdx.x & 63;
-  const bool solver = threadIdx.x < kWave;      // wave 0 solves, wave 1 prepares
+  // wave 0 solves, wave 1 forms edges and their skips, wave 2 old nodes' arrivals and
+  // the memory sums, wave 3 the device chains
+  const int role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int g = blockIdx.x / a.K, k = blockIdx.x % a.K;
   const int g0 = wt.ptr[g], ng = wt.ptr[g + 1] - g0;
   const int w0 = wt.blk[g], nw = wt.blk[g + 1] - w0;
@@ -193,59 +216,95 @@ __global__ __launch_bounds__(128) void k_list_schedule(EvalArgs a, GraphTable wt
   unsigned* far = a.far + (size_t)k * a.far_stride + g0;
   const bool use_far = ng > R;                  // nodes older than the ring are read back
   if (threadIdx.x < GDP_MAX_DEVICES) dev_free[threadIdx.x] = 0u;
-  for (int i = threadIdx.x; i < GDP_MAX_DEVICES * kMemSpread; i += 128) (&mem[0][0])[i] = 0ull;
+  for (int i = threadIdx.x; i < GDP_MAX_DEVICES * kMemSpread; i += 256) (&mem[0][0])[i] = 0ull;
   if (threadIdx.x == 0) side_wrapped = 0;
   bool wrapped = false;
+  auto device_of = [&](int p) { return p >= 0 && p < a.D ? (unsigned)p : 0u; };
+  // the window's own 64 nodes: placement or any per-node word, loaded a window ahead
+  auto place_of = [&](int w) { return w * kWin + lane < ng ? prow[w * kWin + lane] : -1; };
+  // (a vector load: a scalar one would share the counter that LDS results are waited on with)
+  int vzero;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
+  auto win_of = [&](int w) { return w < nw ? a.win[w0 + w + vzero] : make_int4(0, 0, 0, 0); };
 
-  // wave 1: inputs of the window being prepared (nxt) and of the one before it
-  struct Side {
-    int4 h;
-    unsigned p;        // device (0 where the placement is out of range)
-    bool counted;      // a real node on a device in range
-    int m;
-  };
-  auto load_side = [&](int w) {
-    Side s = {make_int4(0, 0, -1, -1), 0u, false, 0};
-    const int v = w * kWin + lane;
-    if (w < nw && v < ng) {
-      s.h = hrow[v];
-      const int p = prow[v];
-      s.counted = p >= 0 && p < a.D;
-      s.p = s.counted ? (unsigned)p : 0u;
-      s.m = mrow[v];
-    }
-    return s;
-  };
-  constexpr int kAhead = 3;                     // record chunks of 64 loaded a window ahead
-  int2 rq[kAhead];
-  int4 wq = make_int4(0, 0, 0, 0);
-  Side cur, nxt;
-  unsigned prev_p = 0u, prev_x = 0u;
-  auto load_win = [&](int w) {
-    wq = w < nw ? a.win[w0 + w] : make_int4(0, 0, 0, 0);
-#pragma unroll
-    for (int c = 0; c < kAhead; ++c)
-      if (c * kWave + lane < wq.y) rq[c] = a.rec[wq.x + c * kWave + lane];
-  };
+  // Both of a window's edge waves: what a successor needs of a node (out_xfer and
+  // device in one word), and the edge word of source word `src` in lane l.
+  auto own_of = [&](int4 h, unsigned p) { return pack(min((unsigned)h.y, kTimeLimit - 1u), p); };
+  auto moves = [&](unsigned src, unsigned l, unsigned p) { return l != kNone && (src & 63u) != p; };
 
-  // wave 1: window w's lists into buf[w & 1]; every node before window w - 1 is final
-  auto prepare = [&](int w) {
+  // ---- wave 1: window w's own edges into buf[w & 1] ----------------------------
+  int4 l_hdr = make_int4(0, 0, -1, -1), l_win = make_int4(0, 0, 0, 0);
+  int l_p = -1;
+  auto load_lists = [&](int w) {
+    l_hdr = w * kWin + lane < ng ? hrow[w * kWin + lane] : make_int4(0, 0, -1, -1);
+    l_p = place_of(w);
+    l_win = win_of(w);
+  };
+  auto form_lists = [&](int w) {
+    const int4 h = l_hdr, wn = l_win;          // wn: the same in every lane
+    const unsigned p = device_of(l_p);
+    load_lists(w + 1);
     WinBuf& B = buf[w & 1];
-    cur = nxt;
-    const int4 wn = make_int4(__builtin_amdgcn_readfirstlane(wq.x), __builtin_amdgcn_readfirstlane(wq.y),
-                              __builtin_amdgcn_readfirstlane(wq.z), __builtin_amdgcn_readfirstlane(wq.w));
-    int2 rc[kAhead];
+    const bool live = w * kWin + lane < ng;
+    const unsigned cost = min((unsigned)h.x, kTimeLimit - 1u);
+    wrapped |= live && (unsigned)h.x >= kTimeLimit;
+    const unsigned own = own_of(h, p);
+    unsigned in[kSlots], src[kSlots];
 #pragma unroll
-    for (int c = 0; c < kAhead; ++c) rc[c] = rq[c];
-    nxt = load_side(w + 1);
-    load_win(w + 1);
-    const int v0 = w * kWin;
-    const bool live = v0 + lane < ng;
-    const unsigned p = cur.p;
-    unsigned cost = (unsigned)cur.h.x, xfer = (unsigned)cur.h.y;
-    if (cost >= kTimeLimit) { wrapped |= live; cost = kTimeLimit - 1u; }
-    // device chain: the previous and the following lanes on the same device
-    uint64_t same = __ballot(live);
+    for (int q = 0; q < kSlots; ++q) src[q] = lane_at(own, ((unsigned)h.z >> (8 * q)) & 63u);
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      const unsigned l = ((unsigned)h.z >> (8 * q)) & 0xffu;
+      const unsigned wgt = (moves(src[q], l, p) ? src[q] >> 6 : 0u) + cost;
+      wrapped |= l != kNone && wgt >= kTimeLimit;
+      in[q] = l == kNone ? (unsigned)lane : pack(min(wgt, kTimeLimit - 1u), l);
+    }
+    const uint64_t bigs = __ballot((unsigned)h.y >= kTimeLimit);
+    if (bigs != 0ull) {                        // transfers of 2^26 and more
+#pragma unroll
+      for (int q = 0; q < kSlots; ++q) {
+        const unsigned l = ((unsigned)h.z >> (8 * q)) & 0xffu;
+        wrapped |= moves(src[q], l, p) && ((bigs >> (l & 63u)) & 1ull);
+      }
+    }
+    // skips of 2, 4 and 8 along the latest predecessors, where the window uses them
+    unsigned sk[3] = {0u, 0u, 0u};
+    if (__builtin_amdgcn_readfirstlane(wn.w) & kDeepBit) {
+      unsigned sp = in[0] & 63u, ss = in[0] >> 6;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const unsigned s2 = lane_at(ss, sp), sp2 = lane_at(sp, sp);
+        ss += s2;
+        sp = sp2;
+        wrapped |= ss >= kTimeLimit;
+        ss = min(ss, kTimeLimit - 1u);
+        sk[i] = pack(ss, sp);
+      }
+    }
+    B.in[lane] = make_uint4(in[0], in[1], in[2], in[3]);
+    B.skip[lane] = make_uint4(sk[0], sk[1], sk[2], pack(cost, p));
+    if (lane == 0) B.w = make_uint4((unsigned)wn.w & 127u, (unsigned)wn.z, (unsigned)(wn.z + (wn.w >> 7)), 0u);
+  };
+
+  // ---- wave 3: window w's device chains and edges from window w - 1 -------------
+  int4 c_hdr = make_int4(0, 0, -1, -1);
+  int c_p = -1;
+  unsigned prev_own = 0u;
+  uint64_t prev_bigs = 0ull;
+  auto load_chains = [&](int w) {
+    c_hdr = w * kWin + lane < ng ? hrow[w * kWin + lane] : make_int4(0, 0, -1, -1);
+    c_p = place_of(w);
+  };
+  auto form_chains = [&](int w) {
+    const int4 h = c_hdr;
+    const unsigned p = device_of(c_p), cost = min((unsigned)h.x, kTimeLimit - 1u);
+    load_chains(w + 1);
+    WinBuf& B = buf[w & 1];
+    const bool live = w * kWin + lane < ng;
+    unsigned nr[kSlots], src[kSlots];
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) src[q] = lane_at(prev_own, ((unsigned)h.w >> (8 * q)) & 63u);
+    uint64_t same = __ballot(live);             // lanes on the same device
     for (int b = 0; b < a.dev_bits; ++b) {
       const bool bit = (p >> b) & 1u;
       const uint64_t m = __ballot(bit);
@@ -253,193 +312,239 @@ __global__ __launch_bounds__(128) void k_list_schedule(EvalArgs a, GraphTable wt
     }
     const uint64_t below = same & ((1ull << lane) - 1ull);
     const uint64_t last = __ballot(live && (same >> lane) == 1ull);
-    unsigned ptr = live && below ? 63u - (unsigned)__builtin_clzll(below) : (unsigned)lane;
-    unsigned sum = live && below ? cost : 0u;
-    unsigned ch[4];
+    const bool chained = live && below;
+    unsigned cp = chained ? 63u - (unsigned)__builtin_clzll(below) : (unsigned)lane;
+    unsigned cs = chained ? cost : 0u;
+    unsigned ch[5];
+    ch[0] = pack(cs, cp);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i > 0) {
-        const unsigned s2 = lane_at(sum, ptr);
-        ptr = lane_at(ptr, ptr);
-        sum += s2;
-        if (sum >= kTimeLimit) { wrapped = true; sum = kTimeLimit - 1u; }
-      }
-      ch[i] = pack(sum, ptr);
+    for (int i = 1; i < 5; ++i) {               // 2, 4, 8 and 16 ops back
+      const unsigned c2 = lane_at(cs, cp), cp2 = lane_at(cp, cp);
+      cs += c2;
+      cp = cp2;
+      wrapped |= cs >= kTimeLimit;
+      cs = min(cs, kTimeLimit - 1u);
+      ch[i] = pack(cs, cp);
     }
-    // edges from this window and from the one before
-    unsigned in[kSlots], nr[kSlots];
-    const int n_in = wn.w & 7, n_near = (wn.w >> 3) & 7;
 #pragma unroll
     for (int q = 0; q < kSlots; ++q) {
-      in[q] = (unsigned)lane;
-      nr[q] = ~0u;
-      if (q < n_in) {
-        const unsigned l = ((unsigned)cur.h.z >> (8 * q)) & 0xffu;
-        const unsigned pu = lane_at(p, l & 63u), xu = lane_at(xfer, l & 63u);
-        if (l != kNone) {
-          unsigned wgt = pu != p ? xu : 0u;
-          if (wgt >= kTimeLimit) wgt = kTimeLimit;
-          wgt += cost;
-          if (wgt >= kTimeLimit) { wrapped = true; wgt = kTimeLimit - 1u; }
-          in[q] = pack(wgt, l);
-        }
-      }
-      if (q < n_near) {
-        const unsigned l = ((unsigned)cur.h.w >> (8 * q)) & 0xffu;
-        const unsigned pu = lane_at(prev_p, l & 63u), xu = lane_at(prev_x, l & 63u);
-        if (l != kNone) {
-          unsigned wgt = pu != p ? xu : 0u;
-          if (wgt >= kTimeLimit) { wrapped = true; wgt = kTimeLimit - 1u; }
-          nr[q] = pack(wgt, l);
-        }
-      }
+      const unsigned l = ((unsigned)h.w >> (8 * q)) & 0xffu;
+      const bool moved = moves(src[q], l, p);
+      nr[q] = l == kNone ? ~0u : pack(moved ? src[q] >> 6 : 0u, l);
+      if (prev_bigs != 0ull) wrapped |= moved && ((prev_bigs >> (l & 63u)) & 1ull);
     }
-    // skips along the latest predecessors
-    unsigned sk[3];
-    ptr = in[0] & 63u;
-    sum = in[0] >> 6;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      if (n_in > 0) {
-        const unsigned s2 = lane_at(sum, ptr);
-        ptr = lane_at(ptr, ptr);
-        sum += s2;
-        if (sum >= kTimeLimit) { wrapped = true; sum = kTimeLimit - 1u; }
-      }
-      sk[i] = pack(sum, ptr);
-    }
-    B.in[lane] = make_uint4(in[0], in[1], in[2], in[3]);
     B.near[lane] = make_uint4(nr[0], nr[1], nr[2], nr[3]);
     B.chain[lane] = make_uint4(ch[0], ch[1], ch[2], ch[3]);
-    B.skip[lane] = make_uint4(sk[0], sk[1], sk[2], pack(cost, p));
-    B.ready[lane] = 0u;
-    if (lane == 0) {
-      B.last_lo = (unsigned)last;
-      B.last_hi = (unsigned)(last >> 32);
-      B.slots = wn.w & 63;
-      B.extra0 = wn.z;
-      B.extra1 = wn.z + (wn.w >> 6);
-    }
-    // arrivals from old nodes
-    for (int c = 0; c * kWave < wn.y; ++c) {
-      const int e = c * kWave + lane;
-      const bool ok = e < wn.y;
-      int2 r = make_int2(0, 0);
-      if (c < kAhead) {
-        r = c == 0 ? rc[0] : c == 1 ? rc[1] : rc[2];
-      } else if (ok) {
-        r = a.rec[wn.x + e];
-      }
-      const int u = r.x & 0x7fffffff;
-      const unsigned lv = (unsigned)r.y & 63u, x = (unsigned)r.y >> 6;
-      const unsigned pv = lane_at(p, lv);
-      if (ok) {
-        // the solver is writing window w - 1 into the ring
-        unsigned word;
-        if (u >= v0 - R) word = ring[u & (R - 1)];
-        else word = load_wait(&far[u]);
-        const bool moved = (word & 63u) != pv;
-        if (moved && r.x < 0) wrapped = true;
-        atomicMax(&B.ready[lv], (word >> 6) + (moved ? x : 0u));
-      }
-    }
-    if (cur.counted) atomicAdd(&mem[p][lane & (kMemSpread - 1)], (unsigned long long)(uint32_t)cur.m);
-    prev_p = p;
-    prev_x = xfer;
+    B.chain16[lane] = ch[4];
+    if (lane == 0) B.last = make_uint2((unsigned)last, (unsigned)(last >> 32));
+    prev_own = own_of(h, p);
+    prev_bigs = __ballot((unsigned)h.y >= kTimeLimit);
   };
 
-  if (!solver) {
-    nxt = load_side(0);
-    load_win(0);
-  }
-  __syncthreads();                              // the tables above are cleared
-  if (!solver) prepare(0);
+  // ---- wave 2: arrivals at window w from the nodes before window w - 1 --------
+  constexpr int kAhead = 3;                     // record chunks of 64 loaded a window ahead
+  int2 o_rec[kAhead];
+  int4 o_win = make_int4(0, 0, 0, 0), o_next = make_int4(0, 0, 0, 0);
+  int o_p = -1, o_m = 0;
+  auto load_old = [&](int w) {                  // window w's placements, sums and records, window w + 1's extent
+    o_p = place_of(w);
+    o_m = w * kWin + lane < ng ? mrow[w * kWin + lane] : 0;
+    o_win = o_next;
+    o_next = win_of(w + 1);
+#pragma unroll
+    for (int c = 0; c < kAhead; ++c) {
+      o_rec[c] = make_int2(0, 0);
+      if (c * kWave + lane < o_win.y) o_rec[c] = a.rec[o_win.x + c * kWave + lane];
+    }
+  };
+  auto old_arrivals = [&](int w) {
+    int2 rc[kAhead];
+#pragma unroll
+    for (int c = 0; c < kAhead; ++c) rc[c] = o_rec[c];
+    const int pr = o_p, m = o_m;
+    const unsigned p = device_of(pr);
+    const int base = __builtin_amdgcn_readfirstlane(o_win.x), n_old = __builtin_amdgcn_readfirstlane(o_win.y);
+    load_old(w + 1);
+    unsigned* rdy = ready[w & 1];
+    const int v0 = w * kWin;
+    rdy[lane] = 0u;
+    unsigned pv[kAhead], word[kAhead];
+#pragma unroll
+    for (int c = 0; c < kAhead; ++c) {
+      pv[c] = lane_at(p, (unsigned)rc[c].y & 63u);
+      word[c] = ring[rc[c].x & (R - 1)];
+    }
+    // the solver is writing window w - 1 into the ring; nodes R and more behind v0 are in memory
+    auto arrive = [&](int2 r, bool ok, unsigned dv, unsigned wd) {
+      const int u = r.x & 0x7fffffff;
+      if (use_far && ok && u < v0 - R) wd = load_wait(&far[u]);
+      const bool moved = ok && (wd & 63u) != dv;
+      wrapped |= moved && r.x < 0;
+      if (ok) atomicMax(&rdy[(unsigned)r.y & 63u], (wd >> 6) + (moved ? (unsigned)r.y >> 6 : 0u));
+    };
+#pragma unroll
+    for (int c = 0; c < kAhead; ++c)
+      if (c * kWave < n_old) arrive(rc[c], c * kWave + lane < n_old, pv[c], word[c]);
+    for (int e0 = kAhead * kWave; e0 < n_old; e0 += kWave) {
+      int2 r = make_int2(0, 0);
+      if (e0 + lane < n_old) r = a.rec[base + e0 + lane];
+      arrive(r, e0 + lane < n_old, lane_at(p, (unsigned)r.y & 63u), ring[r.x & (R - 1)]);
+    }
+    if (pr >= 0 && pr < a.D) atomicAdd(&mem[p][lane & (kMemSpread - 1)], (unsigned long long)(uint32_t)m);
+  };
+
+  // ---- wave 0: the fixed point of window w -------------------------------------
   unsigned mk = 0u, fprev = 0u;
-  __syncthreads();
-  for (int w = 0; w < nw; ++w) {
-    if (!solver) {
-      if (w + 1 < nw) prepare(w + 1);
-    } else {
-      const WinBuf& B = buf[w & 1];
-      const uint4 in = B.in[lane], ch = B.chain[lane], sk = B.skip[lane];
-      const unsigned cost = sk.w >> 6, p = sk.w & 63u;
-      const int slots = __builtin_amdgcn_readfirstlane(B.slots);
-      const int n_in = slots & 7, n_near = slots >> 3;
-      const int x0 = __builtin_amdgcn_readfirstlane(B.extra0), x1 = __builtin_amdgcn_readfirstlane(B.extra1);
-      const int v0 = w * kWin;
-      const bool live = v0 + lane < ng;
-      unsigned r = max(B.ready[lane], dev_free[p]);
-      if (n_near > 0) {
-        const uint4 nr = B.near[lane];
-        const unsigned t0 = lane_at(fprev, nr.x & 63u), t1 = lane_at(fprev, nr.y & 63u);
-        r = max(r, nr.x == ~0u ? 0u : t0 + (nr.x >> 6));
-        r = max(r, nr.y == ~0u ? 0u : t1 + (nr.y >> 6));
-        if (n_near > 2) {
-          const unsigned t2 = lane_at(fprev, nr.z & 63u), t3 = lane_at(fprev, nr.w & 63u);
-          r = max(r, nr.z == ~0u ? 0u : t2 + (nr.z >> 6));
-          r = max(r, nr.w == ~0u ? 0u : t3 + (nr.w >> 6));
-        }
-      }
-      unsigned f = live ? min(r + cost, kTimeLimit) : 0u;
-      if (x1 > x0) fbuf[lane] = fprev;
-      // the fixed point
-      const unsigned a0 = in.x & 63u, a1 = in.y & 63u, a2 = in.z & 63u, a3 = in.w & 63u;
-      const unsigned c0 = ch.x & 63u, c1 = ch.y & 63u, c2 = ch.z & 63u, c3 = ch.w & 63u;
-      const unsigned s0 = sk.x & 63u, s1 = sk.y & 63u, s2 = sk.z & 63u;
+  Lists now, next;
+  auto read_lists = [&](int w) {
+    const WinBuf& B = buf[w & 1];
+    next.w = B.w;
+    next.last = B.last;
+    next.in = B.in[lane];
+    next.near = B.near[lane];
+    next.chain = B.chain[lane];
+    next.skip = B.skip[lane];
+    next.chain16 = B.chain16[lane];
+  };
+  auto solve_window = [&](int w) {
+    const uint4 in = now.in, nr = now.near, ch = now.chain, sk = now.skip;
+    const unsigned cost = sk.w >> 6, p = sk.w & 63u;
+    const unsigned c16 = now.chain16;
+    const int slots = __builtin_amdgcn_readfirstlane((int)now.w.x);
+    const int x0 = __builtin_amdgcn_readfirstlane((int)now.w.y), x1 = __builtin_amdgcn_readfirstlane((int)now.w.z);
+    const int n_in = slots & 7, n_near = (slots >> 3) & 7;
+    const bool deep = (slots & kDeepBit) != 0;
+    const uint64_t last = (uint64_t)now.last.y << 32 | now.last.x;
+    const int v0 = w * kWin;
+    const bool live = v0 + lane < ng;
+    // flds still holds the previous window's finish times
+    const unsigned t0 = flds[nr.x & 63u], t1 = flds[nr.y & 63u];
+    unsigned r = max(ready[w & 1][lane], dev_free[p]);
+    r = max(r, max(nr.x == ~0u ? 0u : t0 + (nr.x >> 6), nr.y == ~0u ? 0u : t1 + (nr.y >> 6)));
+    if (n_near > 2) {
+      const unsigned t2 = flds[nr.z & 63u], t3 = flds[nr.w & 63u];
+      r = max(r, max(nr.z == ~0u ? 0u : t2 + (nr.z >> 6), nr.w == ~0u ? 0u : t3 + (nr.w >> 6)));
+    }
+    // the next window's lists arrive during this one's repeats
+    if (w + 1 < nw) read_lists(w + 1);
+    unsigned f = live ? min(r + cost, kTimeLimit) : 0u;
+    // Repeats: every lane's edges read in one round, from a copy of f in LDS (a
+    // permute per edge: 322 cycles a repeat at 11 edges against 290).  At most
+    // 63 edges of less than 2^26 each on top of 2^26: no wrap-around before
+    // the clamp that follows.
+    auto repeat = [&](auto edges, auto skips) {
+      constexpr int NE = decltype(edges)::value;      // slots in use
+      constexpr bool SK = decltype(skips)::value;
       bool again = true;
       while (again) {
-        const unsigned old = f;
-        const unsigned h0 = lane_at(f, c0), h1 = lane_at(f, c1), h2 = lane_at(f, c2), h3 = lane_at(f, c3);
+        flds[lane] = f;
+        __builtin_amdgcn_wave_barrier();
+        const unsigned h0 = flds[ch.x & 63u], h1 = flds[ch.y & 63u], h2 = flds[ch.z & 63u], h3 = flds[ch.w & 63u],
+                       h4 = flds[c16 & 63u];
+        unsigned e[kSlots], k[3];
+        e[0] = flds[in.x & 63u];
+        if constexpr (SK) {
+          k[0] = flds[sk.x & 63u];
+          k[1] = flds[sk.y & 63u];
+          k[2] = flds[sk.z & 63u];
+        }
+        if constexpr (NE > 1) e[1] = flds[in.y & 63u];
+        if constexpr (NE > 2) {
+          e[2] = flds[in.z & 63u];
+          e[3] = flds[in.w & 63u];
+        }
         unsigned best = max(max(h0 + (ch.x >> 6), h1 + (ch.y >> 6)), max(h2 + (ch.z >> 6), h3 + (ch.w >> 6)));
-        if (n_in > 0) {
-          const unsigned e0 = lane_at(old, a0), k0 = lane_at(old, s0), k1 = lane_at(old, s1), k2 = lane_at(old, s2);
-          best = max(best, max(max(e0 + (in.x >> 6), k0 + (sk.x >> 6)), max(k1 + (sk.y >> 6), k2 + (sk.z >> 6))));
-          if (n_in > 1) {
-            const unsigned e1 = lane_at(old, a1), e2 = lane_at(old, a2), e3 = lane_at(old, a3);
-            best = max(best, max(e1 + (in.y >> 6), max(e2 + (in.z >> 6), e3 + (in.w >> 6))));
-          }
-        }
-        f = min(max(f, best), kTimeLimit);
-        if (x1 > x0) {
-          // edges beyond the slots: by records, through LDS
-          fbuf[kWin + lane] = f;
-          arr[lane] = 0u;
-          __builtin_amdgcn_wave_barrier();
-          for (int e = x0 + lane; e < x1; e += kWave) {
-            const int2 q = a.rec[e];
-            const int u = q.x & 0x7fffffff;
-            const unsigned lv = (unsigned)q.y & 63u;
-            const int pu = prow[u], pv = prow[v0 + (int)lv];
-            const unsigned du = pu >= 0 && pu < a.D ? (unsigned)pu : 0u, dv = pv >= 0 && pv < a.D ? (unsigned)pv : 0u;
-            if (du != dv && q.x < 0) wrapped = true;
-            atomicMax(&arr[lv], fbuf[u - v0 + kWin] + (du != dv ? (unsigned)q.y >> 6 : 0u));
-          }
-          __builtin_amdgcn_wave_barrier();
-          const unsigned t = arr[lane];
-          if (t != 0u) f = max(f, min(t + cost, kTimeLimit));
-        }
-        again = __any(f != old);
+        best = max(best, max(h4 + (c16 >> 6), e[0] + (in.x >> 6)));
+        if constexpr (SK) best = max(best, max(k[0] + (sk.x >> 6), max(k[1] + (sk.y >> 6), k[2] + (sk.z >> 6))));
+        if constexpr (NE > 1) best = max(best, e[1] + (in.y >> 6));
+        if constexpr (NE > 2) best = max(best, max(e[2] + (in.z >> 6), e[3] + (in.w >> 6)));
+        again = __any(best > f);
+        f = max(f, best);
+        __builtin_amdgcn_wave_barrier();
       }
-      wrapped |= f >= kTimeLimit;
-      mk = max(mk, f);
-      const uint64_t last = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane(B.last_hi) << 32 |
-                            (unsigned)__builtin_amdgcn_readfirstlane(B.last_lo);
-      if ((last >> lane) & 1ull) dev_free[p] = f;
-      const unsigned word = pack(f & (kTimeLimit - 1u), p);
-      if (live) ring[(v0 + lane) & (R - 1)] = word;
-      if (use_far) {
-        // at most one store in flight: the previous window's is complete, so
-        // that a read-back of nodes R and more behind finds them written
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (live) far[v0 + lane] = word;
+      f = min(f, kTimeLimit);
+    };
+    auto relax = [&]() {
+      using std::bool_constant;
+      using std::integral_constant;
+      if (deep) {
+        if (n_in == 1) repeat(integral_constant<int, 1>(), bool_constant<true>());
+        else repeat(integral_constant<int, kSlots>(), bool_constant<true>());
+      } else {
+        if (n_in <= 1) repeat(integral_constant<int, 1>(), bool_constant<false>());
+        else if (n_in == 2) repeat(integral_constant<int, 2>(), bool_constant<false>());
+        else repeat(integral_constant<int, kSlots>(), bool_constant<false>());
       }
-      fprev = f;
+    };
+    relax();
+    while (x1 > x0) {
+      // edges beyond the slots: by records, through LDS
+      const unsigned old = f;
+      fbuf[lane] = fprev;
+      fbuf[kWin + lane] = f;
+      arr[lane] = 0u;
+      __builtin_amdgcn_wave_barrier();
+      for (int e = x0 + lane; e < x1; e += kWave) {
+        const int2 q = a.rec[e];
+        const int u = q.x & 0x7fffffff;
+        const unsigned lv = (unsigned)q.y & 63u;
+        const bool moved = device_of(prow[u]) != device_of(prow[v0 + (int)lv]);
+        wrapped |= moved && q.x < 0;
+        atomicMax(&arr[lv], fbuf[u - v0 + kWin] + (moved ? (unsigned)q.y >> 6 : 0u));
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (live) f = max(f, min(arr[lane] + cost, kTimeLimit));
+      if (!__any(f != old)) break;
+      relax();
     }
+    wrapped |= f >= kTimeLimit;               // (then flds, not clamped, no longer matters)
+    mk = max(mk, f);
+    if ((last >> lane) & 1ull) dev_free[p] = f;
+    const unsigned word = pack(f & (kTimeLimit - 1u), p);
+    if (live) ring[(v0 + lane) & (R - 1)] = word;
+    if (use_far) {
+      // at most one store in flight: the previous window's is complete, so
+      // that a read-back of nodes R and more behind finds them written
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (live) far[v0 + lane] = word;
+    }
+    fprev = f;
+    now = next;
+  };
+
+  if (threadIdx.x < kWin) flds[threadIdx.x] = 0u;
+  if (role == 1) load_lists(0);
+  if (role == 3) load_chains(0);
+  if (role == 2) {
+    o_next = win_of(0);
+    load_old(0);
+  }
+  __syncthreads();                              // the tables above are cleared
+  if (role == 1) {
+    form_lists(0);
+    if (nw > 1) form_lists(1);
+  } else if (role == 3) {
+    form_chains(0);
+    if (nw > 1) form_chains(1);
+  } else if (role == 2) {
+    old_arrivals(0);
+  }
+  __syncthreads();
+  if (role == 0) {
+    read_lists(0);
+    now = next;
+  }
+  __syncthreads();                              // buf[0] is free for window 2
+  for (int w = 0; w < nw; ++w) {
+    if (role == 0) solve_window(w);
+    else if (role == 1 && w + 2 < nw) form_lists(w + 2);
+    else if (role == 2 && w + 1 < nw) old_arrivals(w + 1);
+    else if (role == 3 && w + 2 < nw) form_chains(w + 2);
     __syncthreads();
   }
-  if (!solver && __any(wrapped) && lane == 0) side_wrapped = 1;
+  if (role != 0 && __any(wrapped) && lane == 0) side_wrapped = 1;
   __syncthreads();
-  if (!solver) return;
+  if (role != 0) return;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) mk = max(mk, (unsigned)__shfl_xor((int)mk, o, kWave));
   const bool over = __any(wrapped) || side_wrapped != 0;
@@ -496,7 +601,7 @@ hipError_t launch_evaluate(const EvalLaunch& L, hipStream_t s) {
   const GraphTable& wt = *L.window_table;
   CapTable caps;
   for (int i = 0; i < GDP_MAX_GRAPHS; ++i) caps.cap[i] = i < wt.n ? L.mem_cap[i] : 0;
-  const dim3 grid((unsigned)wt.n * (unsigned)L.K), block(128);
+  const dim3 grid((unsigned)wt.n * (unsigned)L.K), block(256);
   switch (eval_ring(wt.ptr, wt.n, L.K)) {
     case 32768: hipLaunchKernelGGL((k_list_schedule<32768>), grid, block, 0, s, a, wt, caps); break;
     case 16384: hipLaunchKernelGGL((k_list_schedule<16384>), grid, block, 0, s, a, wt, caps); break;
