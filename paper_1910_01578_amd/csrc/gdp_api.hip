@@ -867,7 +867,6 @@ namespace {
 inline void set_bias(tr::GemmStrided<float, float>& g, const float* b) { g.bias_f = b; }
 inline void set_bias(tr::GemmStrided<bf16, bf16>& g, const bf16* b) { g.bias_h = b; }
 inline void set_bias(tr::GemmStrided<float, bf16>& g, const bf16* b) { g.bias_h = b; }
-inline void set_bias(tr::GemmStrided<bf16, float>& g, const float* b) { g.bias_f = b; }
 
 struct TrainCtx {
   hipStream_t st;
@@ -880,10 +879,10 @@ struct TrainCtx {
   int graph_chunks;
 };
 
-// C[M, N] (+)= act(A[M, K] W[N, K]^T + bias): a linear layer on row-major activations.
+// C[M, N] (+)= act(A[M, K] W[N, K]^T + bias) (+ res): a linear layer on row-major activations.
 template <typename TA, typename TW>
 hipError_t lin(const TA* A, int lda, const TW* W, int ldw, const TW* bias, int M, int N, int K, float* C, int ldc,
-               int act, bool acc, const TrainCtx& cx) {
+               int act, bool acc, const TrainCtx& cx, const float* res = nullptr) {
   tr::GemmStrided<TA, TW> g;
   g.a = A; g.sam = lda; g.sak = 1;
   g.b = W; g.sbk = 1; g.sbn = ldw;
@@ -891,20 +890,22 @@ hipError_t lin(const TA* A, int lda, const TW* W, int ldw, const TW* bias, int M
   g.c = C; g.ldc = ldc;
   if (bias) set_bias(g, bias);
   g.act = act;
+  g.res = res; g.ldr = ldc;
   g.accumulate = acc;
   return tr::launch_gemm_strided(g, nullptr, 0, cx.st);
 }
 
-// C[M, N] (+)= (dY[M, K] W[K, N]) masked where mask <= 0: a linear layer's input gradient.
+// C[M, N] (+)= (dY[M, K] W[K, N]) masked where mask <= 0 (+ res): a linear layer's input gradient.
 template <typename TW>
 hipError_t lin_dx(const float* dY, int ldy, const TW* W, int ldw, int M, int N, int K, float* C, int ldc,
-                  const float* mask, int ldm, bool acc, const TrainCtx& cx) {
+                  const float* mask, int ldm, bool acc, const TrainCtx& cx, const float* res = nullptr) {
   tr::GemmStrided<float, TW> g;
   g.a = dY; g.sam = ldy; g.sak = 1;
   g.b = W; g.sbk = ldw; g.sbn = 1;
   g.M = M; g.N = N; g.K = K;
   g.c = C; g.ldc = ldc;
   g.mask = mask; g.ldm = ldm;
+  g.res = res; g.ldr = ldc;
   g.accumulate = acc;
   return tr::launch_gemm_strided(g, nullptr, 0, cx.st);
 }
@@ -1036,8 +1037,7 @@ int train_forward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer*
       GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_attn_fwd(qkv, N, d, p->n_heads, p->seg_len, p->mem_len, gt, O,
                                                       S(tp.lse_att[l]), st));
       GDP_LAUNCH(GDP_K_TRAIN_FWD, lin<float, T>(O, d, static_cast<const T*>(Ly.w_o), d, static_cast<const T*>(Ly.b_o),
-                                                N, d, d, R1, d, tr::ACT_NONE, false, cx));
-      GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_ew(tr::EW_ADD, R1, Y, nullptr, (size_t)N * d, R1, st));
+                                                N, d, d, R1, d, tr::ACT_NONE, false, cx, Y));
       GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_ln_fwd<T>(R1, N, d, static_cast<const T*>(Ly.ln1_g),
                                                        static_cast<const T*>(Ly.ln1_b), Z, st));
       ffn_in = Z;
@@ -1049,8 +1049,7 @@ int train_forward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer*
                                               cx));
     GDP_LAUNCH(GDP_K_TRAIN_FWD, lin<float, T>(H1, dff, static_cast<const T*>(Ly.w_2), dff,
                                               static_cast<const T*>(Ly.b_2), N, d, dff, R2, d, tr::ACT_NONE, false,
-                                              cx));
-    GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_ew(tr::EW_ADD, R2, ffn_in, nullptr, (size_t)N * d, R2, st));
+                                              cx, ffn_in));
     GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_ln_fwd<T>(R2, N, d, static_cast<const T*>(Ly.ln2_g),
                                                      static_cast<const T*>(Ly.ln2_b), S(tp.X[l + 1]), st));
   }
@@ -1101,8 +1100,7 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
     GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, S(tp.H1[l]), dff, d, dff, N, Gl.w_2, dff, false, cx));
     GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dR, d, nullptr, 0, d, Gl.b_2, false, cx));
     GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dH, dff, static_cast<const T*>(Ly.w_1), d, N, d, dff, dZ, d, nullptr, 0, false,
-                                         cx));
-    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ew(tr::EW_ADD, dZ, dR, nullptr, (size_t)N * d, dZ, st));
+                                         cx, dR));
     GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dH, dff, ffn_in, d, dff, d, N, Gl.w_1, d, false, cx));
     GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dH, dff, nullptr, 0, dff, Gl.b_1, false, cx));
     const float* dYp = dZ;   // the gradient reaching Y
@@ -1129,8 +1127,7 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
       GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dkvm, 2 * d, nullptr, 0, 2 * d, Gl.b_qkv + d, true, cx));
       // dY = dR1 + [dQ | dK | dV]_live W_qkv (the memory's part stops at the weights)
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dqkv, 3 * d, static_cast<const T*>(Ly.w_qkv), d, N, d, 3 * d, dY, d, nullptr,
-                                           0, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ew(tr::EW_ADD, dY, dR, nullptr, (size_t)N * d, dY, st));
+                                           0, false, cx, dR));
       dYp = dY;
     }
     // FiLM: dX = gamma dY; dgamma[g] = sum_g dY X, dbeta[g] = sum_g dY

@@ -1,0 +1,474 @@
+// The update step's dense products, C(m, n) = epi(sum_k A(m, k) B(k, n)), in
+// fp32 accuracy on the bf16 matrix cores.
+//
+// An fp32 value is the exact sum of three bf16 values (8 significant bits
+// each), a = a1 + a2 + a3 by repeated round-to-nearest, and the product of two
+// bf16 values is exact in fp32.  With a bf16 B (the weights of a bf16 policy)
+// the three products a1 b + a2 b + a3 b are the whole product; with an fp32 B
+// the six products of weight 2^-16 and above are formed (the three left out are
+// below 2^-26 of |a b| each).  Accumulation is the matrix cores' fp32.  The
+// bf16 instructions do 16 times the work of the fp32 ones per cycle, so three
+// products cost 3/16 and six 3/8 of the fp32 instructions.
+//
+// A work-group (4 waves, 2 x 2) owns a BM x BM tile of C, each wave a (BM/2)^2
+// block.  k advances in steps of KS through two LDS buffers: while a wave's
+// matrix instructions work on step s from one, its vector ALU splits step s + 1
+// into bf16 planes for the other, and the loads of step s + 3 go out into the
+// registers that frees (the memory's latency is two steps).  One barrier a step.
+// KS is 32 (16x16x32 instructions) where k is the operands' fast dimension and
+// 16 (32x32x16; half the LDS, three work-groups a CU) for weight gradients,
+// whose k is the row.  Planes are [row][KS k]; the 16-byte granules of a row are
+// permuted so that eight consecutive rows of a fragment read fall in distinct
+// granules modulo 128 bytes.  Products are formed transposed, so a lane holds 4
+// consecutive n of one m.  With splits > 1 each split of k writes its raw sums
+// to partial[z]; k_gemm_reduce adds them in split order, in double, and applies
+// the epilogue.
+//
+// What bounds it: the split's vector work, the LDS traffic and the matrix
+// instructions of a step are about equal (600 - 800 cycles each), and two
+// work-groups a CU overlap them in part.  At 52,000 rows, 16x16x4 fp32
+// instructions before and this kernel now: weight gradient (256 x 1024) 332 ->
+// 153 us, x W^T (1024 x 256, ReLU) now 118 us (230 TFLOP/s); relative error
+// against float64 2.9e-7 -> 1.6e-7 (k = 256), 5.6e-7 -> 2.4e-7 (weight gradient).
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "device_common.h"
+#include "train_kernels.h"
+
+namespace gdp {
+namespace tr {
+
+namespace {
+
+template <typename T> constexpr int planes() { return sizeof(T) == 2 ? 1 : 3; }
+
+__device__ __forceinline__ float sigmoidf_(float z) { return 1.0f / (1.0f + expf(-z)); }
+
+// Byte offset of 16-byte granule g (8 k values) of a tile row.
+template <int KS>
+__device__ __forceinline__ int tile_at(int row, int g) {
+  if constexpr (KS == 32) return row * 64 + ((g ^ (((row >> 2) ^ (row >> 1)) & 3)) << 4);
+  else return row * 32 + ((g ^ ((row >> 2) & 1)) << 4);
+}
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Eight values as 1 or 3 bf16 planes of 16 bytes at byte offset `at`, planes
+// `plane` bytes apart.
+__device__ __forceinline__ void store_planes(char* s, int at, int plane, const float (&v)[8]) {
+  union P8 {
+    bf16x2 h[4];
+    uint4 q;
+  } p1, p2, p3;
+  // An infinity's remainder is inf - inf: the median turns it into a finite
+  // value beyond any real remainder (at most 2^119), so infinity stays infinity.
+  constexpr float kBig = 2.6584559915698317e36f;   // 2^121
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x2 a = {v[2 * i], v[2 * i + 1]};
+    p1.h[i] = __builtin_convertvector(a, bf16x2);
+    f32x2 r = a - __builtin_convertvector(p1.h[i], f32x2);
+    r[0] = __builtin_amdgcn_fmed3f(r[0], -kBig, kBig);
+    r[1] = __builtin_amdgcn_fmed3f(r[1], -kBig, kBig);
+    p2.h[i] = __builtin_convertvector(r, bf16x2);
+    p3.h[i] = __builtin_convertvector(r - __builtin_convertvector(p2.h[i], f32x2), bf16x2);
+  }
+  *reinterpret_cast<uint4*>(s + at) = p1.q;
+  *reinterpret_cast<uint4*>(s + plane + at) = p2.q;
+  *reinterpret_cast<uint4*>(s + 2 * plane + at) = p3.q;
+}
+__device__ __forceinline__ void store_planes(char* s, int at, int plane, const bf16 (&v)[8]) {
+  (void)plane;
+  bf16x8 p;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) p[i] = v[i];
+  *reinterpret_cast<bf16x8*>(s + at) = p;
+}
+
+template <typename T, int N> struct alignas(sizeof(T) * N) Pack { T v[N]; };
+
+// A tile of R rows x KS k in registers: element (r, k) = p[r * sr + k * sk].
+// KF: sk == 1, a unit is one row's 8 consecutive k.  Else sr == 1 and a unit is
+// 8 k of one row (fp32; a wave's lanes hold consecutive rows) or of two rows
+// (bf16).  Loads are unconditional, so that they stay in flight across the
+// steps: rows at or past rmax are copies of the last one (their results are not
+// stored), k at or past kmax of the last k, which zero_tail() clears.  VEC:
+// aligned for vector loads, and with KF every step is whole (host-checked).
+template <typename T, int R, int KS, bool KF, bool VEC>
+struct Stage {
+  static constexpr int G = KS / 8;                          // granules per row
+  static constexpr int P = !KF && sizeof(T) == 2 ? 2 : 1;   // rows per unit
+  static constexpr int kUnits = R / P * G;                  // fewer than 256: threads share units
+  static constexpr int U = (kUnits + 255) / 256;
+  T v[U][P][8];
+  static __device__ __forceinline__ int unit(int u) {
+    return ((int)threadIdx.x + 256 * u) % (kUnits < 256 ? kUnits : 256 * U);
+  }
+  static __device__ __forceinline__ int row(int u) { return KF ? unit(u) / G : unit(u) % (R / P) * P; }
+  static __device__ __forceinline__ int gran(int u) { return KF ? unit(u) % G : unit(u) / (R / P); }
+  // base: element (r0, k0), rows and ks the rows and k left from there (at least 1)
+  __device__ __forceinline__ void load(const T* base, long sr, long sk, int rows, int ks) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (VEC && KF) {
+        const T* q = base + (unsigned)__mul24(min(row(u), rows - 1), (int)sr) + gran(u) * 8;
+        constexpr int N = 16 / sizeof(T);
+#pragma unroll
+        for (int h = 0; h < 8; h += N) {
+          const Pack<T, N> t = *reinterpret_cast<const Pack<T, N>*>(q + h);
+#pragma unroll
+          for (int i = 0; i < N; ++i) v[u][0][h + i] = t.v[i];
+        }
+      } else if constexpr (VEC) {
+        const int r = min(row(u), rows - P);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const Pack<T, P> t =
+              *reinterpret_cast<const Pack<T, P>*>(base + (unsigned)(__mul24(min(gran(u) * 8 + i, ks - 1), (int)sk) + r));
+#pragma unroll
+          for (int h = 0; h < P; ++h) v[u][h][i] = t.v[h];
+        }
+      } else {
+#pragma unroll
+        for (int h = 0; h < P; ++h)
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            v[u][h][i] = base[(size_t)min(row(u) + h, rows - 1) * sr + (size_t)min(gran(u) * 8 + i, ks - 1) * sk];
+      }
+    }
+  }
+  __device__ __forceinline__ void zero_tail(int ks) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int h = 0; h < P; ++h)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (gran(u) * 8 + i >= ks) v[u][h][i] = (T)0.f;
+  }
+  __device__ __forceinline__ void store(char* s) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int h = 0; h < P; ++h) store_planes(s, tile_at<KS>(row(u) + h, gran(u)), R * KS * 2, v[u][h]);
+  }
+};
+
+// The epilogue as a compile-time set of operations.
+enum Epi { E_RAW = 0, E_BIAS = 1, E_RELU = 2, E_SIGMOID = 4, E_MASK = 8, E_RES = 16, E_ACC = 32 };
+
+template <typename TA, typename TB>
+int epi_of(const GemmStrided<TA, TB>& g) {
+  return (g.bias_f || g.bias_h ? E_BIAS : 0) | (g.act == ACT_RELU ? E_RELU : g.act == ACT_SIGMOID ? E_SIGMOID : 0) |
+         (g.mask ? E_MASK : 0) | (g.res ? E_RES : 0) | (g.accumulate ? E_ACC : 0);
+}
+
+// N consecutive columns from (m, n).
+template <int EPI, int N, typename TA, typename TB>
+__device__ __forceinline__ void epilogue(const GemmStrided<TA, TB>& g, int m, int n, float (&v)[N]) {
+  float* o = g.c + (size_t)m * g.ldc + n;
+  Pack<float, N> t;
+  if constexpr ((EPI & E_BIAS) != 0) {
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] += sizeof(TB) == 2 ? (float)g.bias_h[n + r] : g.bias_f[n + r];
+  }
+#pragma unroll
+  for (int r = 0; r < N; ++r) {
+    if constexpr ((EPI & E_RELU) != 0) v[r] = fmaxf(v[r], 0.f);
+    if constexpr ((EPI & E_SIGMOID) != 0) v[r] = sigmoidf_(v[r]);
+  }
+  if constexpr ((EPI & E_MASK) != 0) {
+    t = *reinterpret_cast<const Pack<float, N>*>(g.mask + (size_t)m * g.ldm + n);
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] = t.v[r] > 0.f ? v[r] : 0.f;
+  }
+  if constexpr ((EPI & E_RES) != 0) {
+    t = *reinterpret_cast<const Pack<float, N>*>(g.res + (size_t)m * g.ldr + n);
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] += t.v[r];
+  }
+  if constexpr ((EPI & E_ACC) != 0) {
+    t = *reinterpret_cast<const Pack<float, N>*>(o);
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] += t.v[r];
+  }
+#pragma unroll
+  for (int r = 0; r < N; ++r) t.v[r] = v[r];
+  *reinterpret_cast<Pack<float, N>*>(o) = t;
+}
+
+}  // namespace
+
+// VEC: vector loads and float4 stores are aligned (host-checked).
+template <typename TA, typename TB, int BM, bool AKF, bool BKF, bool VEC, int EPI>
+__global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, int k_per_split, float* partial, int nt,
+                                                    int mt) {
+  constexpr int KS = AKF || BM == 64 ? 32 : 16;
+  constexpr int MT = KS == 32 ? 16 : 32;                 // rows and columns of one matrix instruction
+  constexpr int WT = BM / 2, NB = WT / MT, PA = planes<TA>(), PB = planes<TB>();
+  constexpr int kPlane = BM * KS * 2, kBuf = (PA + PB) * kPlane;
+  typedef float acc_t __attribute__((ext_vector_type(MT * MT / 64)));
+  __shared__ __attribute__((aligned(16))) char lds[2 * kBuf];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane % MT, gr = lane / MT;
+  const int mw = (wave >> 1) * WT, nw = (wave & 1) * WT;
+  // consecutive tiles of a row block share its rows of A: keep them on one XCD
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int n0 = (tile % nt) * BM, m0 = (tile / nt % mt) * BM, z = tile / (nt * mt);
+  const int kb = z * k_per_split, ke = min(g.K, kb + k_per_split);
+  // Long reductions keep the products below a1 b1 in sums of their own, whose
+  // rounding is 2^-8 of the main one's: one rounding per 16 k instead of six.
+  constexpr bool LO = KS == 16;
+  acc_t acc[NB][NB], low[LO ? NB : 1][LO ? NB : 1];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < MT * MT / 64; ++r) {
+        acc[i][j][r] = 0.f;
+        if constexpr (LO) low[i][j][r] = 0.f;
+      }
+  Stage<TA, BM, KS, AKF, VEC> la[2];
+  Stage<TB, BM, KS, BKF, VEC> lb[2];
+  auto load = [&](auto set, int k) {                     // past the end: the last step again
+    k = min(k, kb + (ke - kb - 1) / KS * KS);
+    la[set].load(g.a + (size_t)m0 * g.sam + (size_t)k * g.sak, g.sam, g.sak, g.M - m0, ke - k);
+    lb[set].load(g.b + (size_t)n0 * g.sbn + (size_t)k * g.sbk, g.sbn, g.sbk, g.N - n0, ke - k);
+  };
+  auto split = [&](auto set, int buf) {
+    la[set].store(lds + buf * kBuf);
+    lb[set].store(lds + buf * kBuf + PA * kPlane);
+  };
+  auto step = [&](auto s, int k) {                       // step k from buffer s; step k + KS into the other
+    constexpr int S = decltype(s)::value;
+    const char* sA = lds + S * kBuf;
+    const char* sB = sA + PA * kPlane;
+    constexpr std::integral_constant<int, 1 - S> other{};
+    if (k + 2 * KS > ke) {                               // the last step, and one more after an odd number
+      la[1 - S].zero_tail(ke - k - KS);
+      lb[1 - S].zero_tail(ke - k - KS);
+    }
+    bf16x8 fb[NB][PB], fa[NB][PA];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+        fb[j][p] = *reinterpret_cast<const bf16x8*>(sB + p * kPlane + tile_at<KS>(nw + MT * j + col, gr));
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int p = 0; p < PA; ++p)
+        fa[i][p] = *reinterpret_cast<const bf16x8*>(sA + p * kPlane + tile_at<KS>(mw + MT * i + col, gr));
+    split(other, 1 - S);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      // smallest products first
+#pragma unroll
+      for (int w = 2; w >= 0; --w)
+#pragma unroll
+        for (int pa = w; pa >= 0; --pa) {
+          const int pb = w - pa;
+          if (pa >= PA || pb >= PB) continue;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            if constexpr (MT == 16) {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], fa[i][pa], acc[i][j], 0, 0, 0);
+            } else {
+              acc_t& c = LO && w > 0 ? low[i][j] : acc[i][j];
+              c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][pb], fa[i][pa], c, 0, 0, 0);
+            }
+          }
+        }
+    load(other, k + 3 * KS);
+    if constexpr (KS == 16) {
+      // Fragment reads first, then the split's vector work in the shadow of the
+      // matrix instructions (201 -> 184 us for 1024 x 256 over 52,000 rows; the
+      // other shape's compiler order is as good).
+      __builtin_amdgcn_sched_group_barrier(0x100, NB * (PA + PB), 0);
+#pragma unroll
+      for (int i = 0; i < NB * NB * (PA * PB == 9 ? 6 : PA * PB); ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+      }
+    }
+    __syncthreads();
+  };
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+  load(c0, kb);
+  load(c1, kb + KS);
+  if (kb + KS > ke) {
+    la[0].zero_tail(ke - kb);
+    lb[0].zero_tail(ke - kb);
+  }
+  split(c0, 0);
+  load(c0, kb + 2 * KS);
+  __syncthreads();
+  for (int k = kb; k < ke; k += 2 * KS) {
+    step(c0, k);
+    step(c1, k + KS);
+  }
+  // lane: row mw + MT i + col of C, groups of 4 columns
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < MT * MT / 256; ++q) {
+        const int m = m0 + mw + MT * i + col;
+        const int n = n0 + nw + MT * j + (MT == 16 ? 4 * gr : 8 * q + 4 * gr);
+        if (m >= g.M || n >= g.N) continue;
+        float v[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        if constexpr (LO) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] += low[i][j][4 * q + r];
+        }
+        float* o = partial + ((size_t)z * g.M + m) * g.N + n;
+        if constexpr (VEC) {
+          if (partial) *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+          else epilogue<EPI, 4>(g, m, n, v);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (n + r >= g.N) break;
+            float w[1] = {v[r]};
+            if (partial) o[r] = v[r];
+            else epilogue<EPI, 1>(g, m, n + r, w);
+          }
+        }
+      }
+}
+
+template <typename TA, typename TB, int EPI>
+__global__ __launch_bounds__(256) void k_gemm_reduce(GemmStrided<TA, TB> g, int splits, const float* partial) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i >= (size_t)g.M * g.N) return;
+  const int m = (int)(i / g.N), n = (int)(i % g.N);
+  double s = 0.0;   // the splits' sums added in double: long reductions (k = rows) keep fp32 accuracy
+  for (int z = 0; z < splits; ++z) s += (double)partial[(size_t)z * g.M * g.N + i];
+  float v[1] = {(float)s};
+  epilogue<EPI, 1>(g, m, n, v);
+}
+
+namespace {
+
+// Vectors of `bytes` bytes along the fast dimension are aligned when the base
+// and the other dimension's stride are multiples of them.
+template <typename T>
+bool vec_aligned(const T* p, long stride, int bytes) {
+  return ((uintptr_t)p % bytes) == 0 && (stride * (long)sizeof(T)) % bytes == 0;
+}
+
+template <typename TA, typename TB, bool AKF, bool BKF, bool VEC, int EPI>
+hipError_t launch_epi(const GemmStrided<TA, TB>& g, int bm, int splits, int kps, float* part, hipStream_t s) {
+  const int nt = (g.N + bm - 1) / bm, mt = (g.M + bm - 1) / bm;
+  const dim3 grid((unsigned)nt * mt * splits), block(256);
+  if constexpr (VEC) {
+    if (bm == 128) {
+      hipLaunchKernelGGL((k_gemm_split<TA, TB, 128, AKF, BKF, VEC, EPI>), grid, block, 0, s, g, kps, part, nt, mt);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_gemm_split<TA, TB, 64, AKF, BKF, VEC, EPI>), grid, block, 0, s, g, kps, part, nt, mt);
+  return hipGetLastError();
+}
+
+template <typename TA, typename TB, bool AKF, bool BKF, int EPI>
+hipError_t launch_form(const GemmStrided<TA, TB>& g, int bm, int splits, int kps, float* part, bool vec, hipStream_t s) {
+  return vec ? launch_epi<TA, TB, AKF, BKF, true, EPI>(g, bm, splits, kps, part, s)
+             : launch_epi<TA, TB, AKF, BKF, false, EPI>(g, bm, splits, kps, part, s);
+}
+
+}  // namespace
+
+template <typename TA, typename TB>
+hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, size_t partial_floats, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  // vector loads along the operands' fast dimension and float4 columns of c
+  const bool akf = g.sak == 1, bkf = g.sbk == 1;
+  bool vec = g.N % 4 == 0 && g.N >= 4 && g.M >= 2 && g.K >= 1;
+  vec = vec && (akf ? g.K % 32 == 0 && vec_aligned(g.a, g.sam, 16) : vec_aligned(g.a, g.sak, 2 * sizeof(TA)));
+  vec = vec && (bkf ? g.K % 32 == 0 && vec_aligned(g.b, g.sbn, 16) : vec_aligned(g.b, g.sbk, 2 * sizeof(TB)));
+  vec = vec && (!partial || vec_aligned(partial, 0, 16));
+  vec = vec && (vec_aligned(g.c, g.ldc, 16) && (!g.mask || vec_aligned(g.mask, g.ldm, 16)) &&
+                (!g.res || vec_aligned(g.res, g.ldr, 16)));
+  if (!akf) vec = vec && g.M % 2 == 0;          // row pairs
+  int bm = 64, splits = 1;
+  if (akf) {
+    // 128 x 128 tiles when they give at least two work-groups per CU, else 64 x 64
+    const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    if (vec && tiles128 >= 512) bm = 128;
+  } else {
+    // A weight gradient: few tiles, long k (the rows).  Pieces of k of 256 to
+    // kMostRows rows, each summed in fp32, the pieces added in double; as many as
+    // make rounds of two work-groups per CU cheapest (at 52,000 rows a step of
+    // 16 takes 1.4 us with the chip full; the pieces' sums cost their traffic).
+    constexpr int kMostRows = 2048, kLeastRows = 256;
+    if (vec && g.M >= 128 && g.N >= 128) bm = 128;
+    const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bm - 1) / bm);
+    const long most = partial ? std::min<long>(std::max(1, g.K / kLeastRows), (long)(partial_floats / ((size_t)g.M * g.N))) : 1;
+    double best = 0.0;
+    for (long n = partial ? std::min<long>(most, (g.K + kMostRows - 1) / kMostRows) : 1; n <= most; ++n) {
+      const double rows = std::max(1.0, std::ceil((double)g.K / n));
+      const double rounds = std::ceil(tiles * n / 512.0);
+      const double us = rounds * (rows / 16 * 1.4 * (bm == 128 ? 1.0 : 0.4) + 8.0) + (n > 1 ? n * (double)g.M * g.N * 8e-6 / 5.0 : 0.0);
+      if (best == 0.0 || us < best) {
+        best = us;
+        splits = (int)n;
+      }
+    }
+  }
+  const int kps = splits > 1 ? (((g.K + splits - 1) / splits + 31) / 32) * 32 : std::max(g.K, 1);
+  splits = splits > 1 ? (g.K + kps - 1) / kps : 1;
+  float* part = splits > 1 ? partial : nullptr;
+  const int epi = epi_of(g);
+  // The forms in use: a linear layer, its input gradient, its weight gradient.
+  hipError_t e = hipErrorInvalidValue;
+#define GDP_GEMM_CASE(E, AKF, BKF) \
+  case E: e = launch_form<TA, TB, AKF, BKF, E>(g, bm, splits, kps, part, vec, s); break
+  if (akf && bkf) {
+    switch (epi) {
+      GDP_GEMM_CASE(E_BIAS, true, true);
+      GDP_GEMM_CASE(E_BIAS | E_RELU, true, true);
+      GDP_GEMM_CASE(E_BIAS | E_SIGMOID, true, true);
+      GDP_GEMM_CASE(E_BIAS | E_RES, true, true);
+      GDP_GEMM_CASE(E_ACC, true, true);
+    }
+  } else if (akf && g.sbn == 1) {
+    if constexpr (std::is_same<TA, float>::value) {
+      switch (epi) {
+        GDP_GEMM_CASE(E_RAW, true, false);
+        GDP_GEMM_CASE(E_MASK, true, false);
+        GDP_GEMM_CASE(E_RES, true, false);
+        GDP_GEMM_CASE(E_ACC, true, false);
+      }
+    }
+  } else if (g.sam == 1 && g.sbn == 1) {
+    if constexpr (std::is_same<TA, float>::value) {
+      switch (epi) {
+        GDP_GEMM_CASE(E_RAW, false, false);
+        GDP_GEMM_CASE(E_ACC, false, false);
+      }
+    }
+  }
+#undef GDP_GEMM_CASE
+  if (e != hipSuccess || splits == 1) return e;
+  const size_t n = (size_t)g.M * g.N;
+  const dim3 rgrid((unsigned)((n + 255) / 256));
+  if (epi == E_RAW) hipLaunchKernelGGL((k_gemm_reduce<TA, TB, E_RAW>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial);
+  else hipLaunchKernelGGL((k_gemm_reduce<TA, TB, E_ACC>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial);
+  return hipGetLastError();
+}
+
+#define GDP_GEMM_INST(TA, TB) \
+  template hipError_t launch_gemm_strided<TA, TB>(const GemmStrided<TA, TB>&, float*, size_t, hipStream_t);
+GDP_GEMM_INST(float, float)
+GDP_GEMM_INST(float, bf16)
+GDP_GEMM_INST(bf16, bf16)
+#undef GDP_GEMM_INST
+
+}  // namespace tr
+}  // namespace gdp

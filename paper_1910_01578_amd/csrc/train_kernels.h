@@ -13,9 +13,10 @@ namespace tr {
 
 enum Act { ACT_NONE = 0, ACT_RELU = 1, ACT_SIGMOID = 2 };
 
-// C(m, n) = epi(alpha * sum_k A(m, k) B(k, n)) with A(m, k) = a[m sam + k sak]
-// and B(k, n) = b[k sbk + n sbn]; epi adds a bias over n (fp32 or bf16),
-// applies act, zeroes where mask[m ldm + n] <= 0, and writes or adds to c.
+// C(m, n) = epi(sum_k A(m, k) B(k, n)) with A(m, k) = a[m sam + k sak] and
+// B(k, n) = b[k sbk + n sbn]; epi adds a bias over n (fp32 or bf16), applies
+// act, zeroes where mask[m ldm + n] <= 0, adds res[m ldr + n], and writes or
+// adds to c (c may be res, not the operands).
 template <typename TA, typename TB>
 struct GemmStrided {
   const TA* a;
@@ -25,12 +26,13 @@ struct GemmStrided {
   int M, N, K;
   float* c;
   long ldc;
-  float alpha = 1.0f;
   const float* bias_f = nullptr;
   const bf16* bias_h = nullptr;
   int act = ACT_NONE;
   const float* mask = nullptr;
   long ldm = 0;
+  const float* res = nullptr;
+  long ldr = 0;
   bool accumulate = false;
 };
 // partial: scratch for split-k sums (partial_floats floats; null: no split).
