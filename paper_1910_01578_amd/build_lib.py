@@ -25,9 +25,10 @@ DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-p
 # Per-file device flags.  Attention applies vector ALU work (softmax scaling)
 # to its MFMA accumulators on every tile: keeping them in ordinary VGPRs
 # avoids a copy to and from the accumulation registers around each use.
-FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-pass-failed"]}
+FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-pass-failed"],
+              "train_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
-SOURCES = ["graph_kernels.hip", "gemm.hip", "layer.hip", "attention.hip", "placer_kernels.hip", "sample.hip", "ppo.hip", "evaluate.hip", "train.hip", "train_gemm.hip",
+SOURCES = ["graph_kernels.hip", "gemm.hip", "layer.hip", "attention.hip", "placer_kernels.hip", "sample.hip", "ppo.hip", "evaluate.hip", "train.hip", "train_gemm.hip", "train_attn.hip",
            "gdp_api.hip", "host_plan.cpp"]
 
 

@@ -1108,7 +1108,7 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
       const float* O = S(tp.O[l]);
       const float* qkv = S(tp.QKV[l]);
       float* dqkv = W(tp.dqkv);
-      float* dkvm = W(tp.dkvm);
+      float* dkva = W(tp.dkva);
       // LN1 and the out-projection: dR = dR1, dO (in dX, free now)
       GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ln_bwd<T>(S(tp.R1[l]), dZ, N, d, static_cast<const T*>(Ly.ln1_g), dR, xg,
                                                       st));
@@ -1118,13 +1118,13 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
                                            cx));
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, O, d, d, d, N, Gl.w_o, d, false, cx));
       GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dR, d, nullptr, 0, d, Gl.b_o, false, cx));
-      // attention: own-segment (live) and memory parts of dK, dV
+      // attention: dK, dV of the own segment (live) and with the memory's part (all)
       GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_attn_bwd(qkv, O, dX, S(tp.lse_att[l]), N, d, p->n_heads, p->seg_len,
-                                                     p->mem_len, gt, W(tp.Dq), dqkv, dkvm, st));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dqkv, 3 * d, Y, d, 3 * d, d, N, Gl.w_qkv, d, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dkvm, 2 * d, Y, d, 2 * d, d, N, Gl.w_qkv + (size_t)d * d, d, true, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dqkv, 3 * d, nullptr, 0, 3 * d, Gl.b_qkv, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dkvm, 2 * d, nullptr, 0, 2 * d, Gl.b_qkv + d, true, cx));
+                                                     p->mem_len, gt, W(tp.Dq), dqkv, dkva, st));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dqkv, 3 * d, Y, d, d, d, N, Gl.w_qkv, d, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dkva, 2 * d, Y, d, 2 * d, d, N, Gl.w_qkv + (size_t)d * d, d, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dqkv, 3 * d, nullptr, 0, d, Gl.b_qkv, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dkva, 2 * d, nullptr, 0, 2 * d, Gl.b_qkv + d, false, cx));
       // dY = dR1 + [dQ | dK | dV]_live W_qkv (the memory's part stops at the weights)
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dqkv, 3 * d, static_cast<const T*>(Ly.w_qkv), d, N, d, 3 * d, dY, d, nullptr,
                                            0, false, cx, dR));

@@ -326,7 +326,7 @@ void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* pl, Tr
   t->xg = carve_add(&c, N * wide * 4);
   t->dH = carve_add(&c, N * dff * 4);
   t->dqkv = carve_add(&c, N * 3 * d * 4);
-  t->dkvm = carve_add(&c, N * 2 * d * 4);
+  t->dkva = carve_add(&c, N * 2 * d * 4);
   t->Dq = carve_add(&c, N * heads * 4);
   t->head_partial = carve_add(&c, ((N + kHeadBwdRows - 1) / kHeadBwdRows) * (size_t)pl->n_devices * (d + 1) * 4);
   t->dfilm = carve_add(&c, (size_t)pl->n_layers * 2 * G * d * 4);

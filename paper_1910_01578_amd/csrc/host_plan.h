@@ -90,7 +90,7 @@ struct TrainPlan {
       lse_att[kMaxTrainPlacerLayers], R1[kMaxTrainPlacerLayers], Z[kMaxTrainPlacerLayers], H1[kMaxTrainPlacerLayers],
       R2[kMaxTrainPlacerLayers];
   // workspace
-  size_t counters, scan_tmp, heavy, dX, dY, dR, dZ, xg, dH, dqkv, dkvm, Dq, head_partial, dfilm, dx0, dh, dA, dP, dU,
+  size_t counters, scan_tmp, heavy, dX, dY, dR, dZ, xg, dH, dqkv, dkva, Dq, head_partial, dfilm, dx0, dh, dA, dP, dU,
       colpart, gemm_partial;
   size_t gemm_partial_floats;
   int chunks;      // 256-row chunks over the graphs (column sums)

@@ -77,11 +77,11 @@ hipError_t launch_sort_rows(const int* ptr, int n, int* idx, hipStream_t s);
 // qkv [n, 3d] fp32; o [n, d]; lse [n, heads].
 hipError_t launch_attn_fwd(const float* qkv, int n, int d, int heads, int seg, int mem, const GraphTable& gt,
                            float* o, float* lse, hipStream_t s);
-// dqkv_live [n, 3d]: dQ and the own-segment dK, dV; dkv_mem [n, 2d]: the dK,
-// dV that later segments' queries send to the row as memory; Dq [n, heads] scratch.
+// dqkv_live [n, 3d]: dQ and the own-segment dK, dV; dkv_all [n, 2d]: those dK,
+// dV plus what later segments' queries send to the row as memory; Dq [n, heads] scratch.
 hipError_t launch_attn_bwd(const float* qkv, const float* O, const float* dO, const float* lse, int n, int d,
                            int heads, int seg, int mem, const GraphTable& gt, float* Dq, float* dqkv_live,
-                           float* dkv_mem, hipStream_t s);
+                           float* dkv_all, hipStream_t s);
 
 template <typename T>
 hipError_t launch_adam(float* master, T* param, const float* grad, float* m, float* v, int64_t n, float lr, float b1,
