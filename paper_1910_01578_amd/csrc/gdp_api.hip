@@ -873,9 +873,9 @@ struct TrainCtx {
   float* partial;          // split-k sums
   size_t partial_floats;
   float* colpart;          // column-sum partials
-  GraphTable rows;         // all rows as one segment (256-row chunks in blk)
+  GraphTable rows;         // all rows as one segment (kColChunkRows-row chunks in blk)
   int row_chunks;
-  GraphTable graphs;       // the graphs, each in 256-row chunks
+  GraphTable graphs;       // the graphs, each in such chunks
   int graph_chunks;
 };
 
@@ -910,23 +910,18 @@ hipError_t lin_dx(const float* dY, int ldy, const TW* W, int ldw, int M, int N, 
   return tr::launch_gemm_strided(g, nullptr, 0, cx.st);
 }
 
-// dW[M, N] (+)= sum over rows r of dY[r][m] X[r][n]: a linear layer's weight gradient.
+// dW[M, N] = sum over rows r of dY[r][m] X[r][n], db[m] = sum of dY[r][m]: a linear
+// layer's weight and bias gradients.
 template <typename TX>
-hipError_t lin_dw(const float* dY, int ldy, const TX* X, int ldx, int M, int N, int rows, float* C, int ldc, bool acc,
+hipError_t lin_dw(const float* dY, int ldy, const TX* X, int ldx, int M, int N, int rows, float* C, int ldc, float* db,
                   const TrainCtx& cx) {
   tr::GemmStrided<float, TX> g;
   g.a = dY; g.sam = 1; g.sak = ldy;
   g.b = X; g.sbk = ldx; g.sbn = 1;
   g.M = M; g.N = N; g.K = rows;
   g.c = C; g.ldc = ldc;
-  g.accumulate = acc;
+  g.rowsum = db;
   return tr::launch_gemm_strided(g, cx.partial, cx.partial_floats, cx.st);
-}
-
-// out[c] (+)= sum over all rows of a[r][c] (* b[r][c])
-template <typename TA>
-hipError_t colsum(const TA* a, int lda, const float* b, int ldb, int C, float* out, bool acc, const TrainCtx& cx) {
-  return tr::launch_colsum(a, lda, b, ldb, C, cx.rows, cx.row_chunks, cx.colpart, out, 0, acc, cx.st);
 }
 
 GraphTable one_segment(int rows, int chunk_rows, int* chunks) {
@@ -992,7 +987,7 @@ int train_forward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer*
     }
     GDP_LAUNCH(GDP_K_TRAIN_FWD, lin<float, T>(A, H, static_cast<const T*>(Lw.w_neigh), H, nullptr, N, H, H, hout, H,
                                               tr::ACT_NONE, true, cx));
-    GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_ew(tr::EW_MASK_POS, hout, hout, nullptr, (size_t)N * H, hout, st));
+    GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_mask_pos(hout, hout, (size_t)N * H, hout, st));
   }
   float* x0 = S(tp.x0);
   {
@@ -1078,7 +1073,6 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
   float* dY = W(tp.dY);
   float* dR = W(tp.dR);
   float* dZ = W(tp.dZ);
-  float* xg = W(tp.xg);
   float* dH = W(tp.dH);
   // the head
   GDP_LAUNCH(GDP_K_BACKWARD, launch_head_backward<T>(S(tp.X[p->n_layers]), static_cast<const T*>(p->w_out), dlogits, N,
@@ -1092,17 +1086,14 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
     const float* Y = S(tp.Y[l]);
     const float* ffn_in = p->attention ? S(tp.Z[l]) : Y;
     // LN2, the FFN and its residual: dZ = dR2 + dH W_1
-    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ln_bwd<T>(S(tp.R2[l]), dX, N, d, static_cast<const T*>(Ly.ln2_g), dR, xg, st));
-    GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(xg, d, nullptr, 0, d, Gl.ln2_g, false, cx));
-    GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dX, d, nullptr, 0, d, Gl.ln2_b, false, cx));
+    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ln_bwd<T>(S(tp.R2[l]), dX, d, static_cast<const T*>(Ly.ln2_g), cx.rows,
+                                                    cx.row_chunks, dR, Gl.ln2_g, Gl.ln2_b, cx.colpart, st));
     GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dR, d, static_cast<const T*>(Ly.w_2), dff, N, dff, d, dH, dff, S(tp.H1[l]),
                                          dff, false, cx));
-    GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, S(tp.H1[l]), dff, d, dff, N, Gl.w_2, dff, false, cx));
-    GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dR, d, nullptr, 0, d, Gl.b_2, false, cx));
+    GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, S(tp.H1[l]), dff, d, dff, N, Gl.w_2, dff, Gl.b_2, cx));
     GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dH, dff, static_cast<const T*>(Ly.w_1), d, N, d, dff, dZ, d, nullptr, 0, false,
                                          cx, dR));
-    GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dH, dff, ffn_in, d, dff, d, N, Gl.w_1, d, false, cx));
-    GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dH, dff, nullptr, 0, dff, Gl.b_1, false, cx));
+    GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dH, dff, ffn_in, d, dff, d, N, Gl.w_1, d, Gl.b_1, cx));
     const float* dYp = dZ;   // the gradient reaching Y
     if (p->attention) {
       const float* O = S(tp.O[l]);
@@ -1110,21 +1101,17 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
       float* dqkv = W(tp.dqkv);
       float* dkva = W(tp.dkva);
       // LN1 and the out-projection: dR = dR1, dO (in dX, free now)
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ln_bwd<T>(S(tp.R1[l]), dZ, N, d, static_cast<const T*>(Ly.ln1_g), dR, xg,
-                                                      st));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(xg, d, nullptr, 0, d, Gl.ln1_g, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dZ, d, nullptr, 0, d, Gl.ln1_b, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ln_bwd<T>(S(tp.R1[l]), dZ, d, static_cast<const T*>(Ly.ln1_g), cx.rows,
+                                                      cx.row_chunks, dR, Gl.ln1_g, Gl.ln1_b, cx.colpart, st));
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dR, d, static_cast<const T*>(Ly.w_o), d, N, d, d, dX, d, nullptr, 0, false,
                                            cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, O, d, d, d, N, Gl.w_o, d, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dR, d, nullptr, 0, d, Gl.b_o, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, O, d, d, d, N, Gl.w_o, d, Gl.b_o, cx));
       // attention: dK, dV of the own segment (live) and with the memory's part (all)
       GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_attn_bwd(qkv, O, dX, S(tp.lse_att[l]), N, d, p->n_heads, p->seg_len,
                                                      p->mem_len, gt, W(tp.Dq), dqkv, dkva, st));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dqkv, 3 * d, Y, d, d, d, N, Gl.w_qkv, d, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dkva, 2 * d, Y, d, 2 * d, d, N, Gl.w_qkv + (size_t)d * d, d, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dqkv, 3 * d, nullptr, 0, d, Gl.b_qkv, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dkva, 2 * d, nullptr, 0, 2 * d, Gl.b_qkv + d, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dqkv, 3 * d, Y, d, d, d, N, Gl.w_qkv, d, Gl.b_qkv, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dkva, 2 * d, Y, d, 2 * d, d, N, Gl.w_qkv + (size_t)d * d, d,
+                                               Gl.b_qkv + d, cx));
       // dY = dR1 + [dQ | dK | dV]_live W_qkv (the memory's part stops at the weights)
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dqkv, 3 * d, static_cast<const T*>(Ly.w_qkv), d, N, d, 3 * d, dY, d, nullptr,
                                            0, false, cx, dR));
@@ -1132,43 +1119,31 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
     }
     // FiLM: dX = gamma dY; dgamma[g] = sum_g dY X, dbeta[g] = sum_g dY
     if (p->film) {
-      const float* gam = film + (size_t)l * 2 * G * d;
       float* dg = dfilm + (size_t)l * 2 * G * d;
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_film_dx(dYp, N, d, gam, gt, dX, st));
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_colsum<float>(dYp, d, Xin, d, d, cx.graphs, cx.graph_chunks, cx.colpart, dg,
-                                                          d, false, st));
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_colsum<float>(dYp, d, nullptr, 0, d, cx.graphs, cx.graph_chunks, cx.colpart,
-                                                          dg + (size_t)G * d, d, false, st));
+      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_film_bwd(dYp, Xin, d, film + (size_t)l * 2 * G * d, cx.graphs,
+                                                     cx.graph_chunks, dX, dg, dg + (size_t)G * d, cx.colpart, st));
     } else {
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_film_dx(dYp, N, d, nullptr, gt, dX, st));
+      std::swap(dX, dYp == dY ? dY : dZ);
     }
   }
   // FiLM weights and the graph embeddings' gradient dx0 [G, H]
   float* dx0 = W(tp.dx0);
-  GDP_LAUNCH(GDP_K_BACKWARD, launch_fill_i32(reinterpret_cast<int*>(dx0), (int64_t)G * H, 0, st));
   if (p->film) {
-    int gch = 0;
-    const GraphTable grows = one_segment(G, tr::kColChunkRows, &gch);
-    const float* x0 = S(tp.x0);
+    FilmLayers<T> fw;
+    tr::FilmWeightGrads fg;
     for (int l = 0; l < p->n_layers; ++l) {
       const gdp_placer_layer& Ly = p->layers[l];
-      const gdp_placer_layer_grad& Gl = gr->placer[l];
-      const float* dg = dfilm + (size_t)l * 2 * G * d;
-      const float* db = dg + (size_t)G * d;
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dg, d, x0, H, d, H, G, Gl.film_wg, H, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(db, d, x0, H, d, H, G, Gl.film_wb, H, false, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_colsum<float>(dg, d, nullptr, 0, d, grows, gch, cx.colpart, Gl.film_bg, 0,
-                                                          false, st));
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_colsum<float>(db, d, nullptr, 0, d, grows, gch, cx.colpart, Gl.film_bb, 0,
-                                                          false, st));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dg, d, static_cast<const T*>(Ly.film_wg), H, G, H, d, dx0, H, nullptr, 0,
-                                           true, cx));
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(db, d, static_cast<const T*>(Ly.film_wb), H, G, H, d, dx0, H, nullptr, 0,
-                                           true, cx));
+      fw.wg[l] = static_cast<const T*>(Ly.film_wg);
+      fw.wb[l] = static_cast<const T*>(Ly.film_wb);
+      fg.wg[l] = gr->placer[l].film_wg;
+      fg.bg[l] = gr->placer[l].film_bg;
+      fg.wb[l] = gr->placer[l].film_wb;
+      fg.bb[l] = gr->placer[l].film_bb;
     }
+    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_film_weights_bwd<T>(fw, fg, p->n_layers, dfilm, S(tp.x0), G, d, H, dx0, st));
   }
   // the GNN: dh of the final embeddings = the placer's input gradient + the mean pool's share of dx0
-  GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_meanpool_bwd(dx0, N, H, gt, dX, st));
+  if (p->film) GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_meanpool_bwd(dx0, N, H, gt, dX, st));
   float* dh_cur = dX;
   float* dh_next = W(tp.dh);
   float* dU = W(tp.dU);
@@ -1179,25 +1154,22 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
     const gdp_gnn_layer& Lw = gnn->layers[l];
     const gdp_gnn_layer_grad& Gl = gr->gnn[l];
     const int hin = l == 0 ? F : H;
-    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ew(tr::EW_MASK_POS, dh_cur, S(tp.h[l + 1]), nullptr, (size_t)N * H, dU, st));
+    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_mask_pos(dh_cur, S(tp.h[l + 1]), (size_t)N * H, dU, st));
     if (l == 0) {
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<T>(dU, H, x, F, H, F, N, Gl.w_self, F, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<T>(dU, H, x, F, H, F, N, Gl.w_self, F, nullptr, cx));
     } else {
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dU, H, S(tp.h[l]), H, H, H, N, Gl.w_self, H, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dU, H, S(tp.h[l]), H, H, H, N, Gl.w_self, H, nullptr, cx));
     }
-    GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dU, H, S(tp.A[l]), H, H, H, N, Gl.w_neigh, H, false, cx));
-    GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dU, H, nullptr, 0, H, Gl.b_upd, false, cx));
+    GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dU, H, S(tp.A[l]), H, H, H, N, Gl.w_neigh, H, Gl.b_upd, cx));
     GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dU, H, static_cast<const T*>(Lw.w_neigh), H, N, H, H, dA, H, nullptr, 0, false,
                                          cx));
     GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_gather_max_bwd(dA, SI(tp.arg[l]), g->row_ptr, g->col_idx, SI(tp.in_ptr),
-                                                         SI(tp.in_idx), N, H, dP, st));
-    GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ew(tr::EW_SIGMOID_GRAD, dP, S(tp.P[l]), nullptr, (size_t)N * H, dP, st));
+                                                         SI(tp.in_idx), S(tp.P[l]), N, H, dP, st));
     if (l == 0) {
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<T>(dP, H, x, F, H, F, N, Gl.w_pool, F, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<T>(dP, H, x, F, H, F, N, Gl.w_pool, F, Gl.b_pool, cx));
     } else {
-      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dP, H, S(tp.h[l]), H, H, H, N, Gl.w_pool, H, false, cx));
+      GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dP, H, S(tp.h[l]), H, H, H, N, Gl.w_pool, H, Gl.b_pool, cx));
     }
-    GDP_LAUNCH(GDP_K_BACKWARD, colsum<float>(dP, H, nullptr, 0, H, Gl.b_pool, false, cx));
     if (l > 0) {
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dx<T>(dU, H, static_cast<const T*>(Lw.w_self), hin, N, hin, H, dh_next, hin,
                                            nullptr, 0, false, cx));
@@ -1338,16 +1310,9 @@ extern "C" int gdp_adam_step(int32_t n_tensors, const gdp_adam_tensor* tensors, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const float c1 = (float)(1.0 - pow((double)beta1, (double)step));
   const float c2 = (float)(1.0 - pow((double)beta2, (double)step));
-  for (int i = 0; i < n_tensors; ++i) {
-    const gdp_adam_tensor& t = tensors[i];
-    if (t.n == 0) continue;
-    if (dtype == GDP_BF16)
-      GDP_LAUNCH(GDP_K_ADAM, tr::launch_adam<bf16>(t.master, static_cast<bf16*>(t.param), t.grad, t.m, t.v, t.n, lr,
-                                                   beta1, beta2, eps, c1, c2, st));
-    else
-      GDP_LAUNCH(GDP_K_ADAM, tr::launch_adam<float>(t.master, static_cast<float*>(t.param), t.grad, t.m, t.v, t.n, lr,
-                                                    beta1, beta2, eps, c1, c2, st));
-  }
+  for (int i = 0; i < n_tensors; i += tr::kAdamTensors)
+    GDP_LAUNCH(GDP_K_ADAM, tr::launch_adam(tensors + i, std::min(tr::kAdamTensors, n_tensors - i), dtype == GDP_BF16, lr,
+                                           beta1, beta2, eps, c1, c2, st));
   return GDP_OK;
 }
 

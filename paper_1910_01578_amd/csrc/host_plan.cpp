@@ -281,7 +281,7 @@ void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* pl, Tr
   const size_t G = (size_t)g->n_graphs, dff = (size_t)pl->d_ff, F = (size_t)g->feat_dim;
   const size_t heads = pl->attention ? (size_t)pl->n_heads : 1;
   int32_t blk[GDP_MAX_GRAPHS + 1];
-  t->chunks = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, 256, blk);
+  t->chunks = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kColSumRows, blk);
   const size_t cap_a = 2 * E, cap_b = N * (size_t)gnn->fanout;
   t->s_cap = (int64_t)(cap_a < cap_b ? cap_a : cap_b);
   Carve c;
@@ -323,7 +323,6 @@ void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* pl, Tr
   t->dY = carve_add(&c, N * d * 4);
   t->dR = carve_add(&c, N * d * 4);
   t->dZ = carve_add(&c, N * d * 4);
-  t->xg = carve_add(&c, N * wide * 4);
   t->dH = carve_add(&c, N * dff * 4);
   t->dqkv = carve_add(&c, N * 3 * d * 4);
   t->dkva = carve_add(&c, N * 2 * d * 4);
@@ -335,11 +334,11 @@ void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* pl, Tr
   t->dA = carve_add(&c, N * H * 4);
   t->dP = carve_add(&c, N * H * 4);
   t->dU = carve_add(&c, N * H * 4);
-  const size_t colw = 3 * d > dff ? 3 * d : dff;
-  t->colpart = carve_add(&c, ((size_t)t->chunks + G) * (colw > fin ? colw : fin) * 4);
+  t->colpart = carve_add(&c, ((size_t)t->chunks + G) * 2 * wide * 4);
   const size_t big = (dff * d > 3 * d * d ? dff * d : 3 * d * d);
-  const size_t splits = (N + 1023) / 1024;   // weight gradients: k = N split into pieces of 1,024 rows
-  t->gemm_partial_floats = (splits > 1 ? splits : 1) * (big > H * fin ? big : H * fin);
+  // weight gradients: k = N split into pieces of at most 2,048 rows, more of them for small matrices
+  const size_t few = (N + 255) / 256 < 8 ? (N + 255) / 256 : 8, splits = (N + 1023) / 1024;
+  t->gemm_partial_floats = (splits > few ? splits : few) * ((big > H * fin ? big : H * fin) + dff + 3 * wide);
   t->gemm_partial = carve_add(&c, t->gemm_partial_floats * 4);
   t->ws_total = c.total;
 }

@@ -90,10 +90,10 @@ struct TrainPlan {
       lse_att[kMaxTrainPlacerLayers], R1[kMaxTrainPlacerLayers], Z[kMaxTrainPlacerLayers], H1[kMaxTrainPlacerLayers],
       R2[kMaxTrainPlacerLayers];
   // workspace
-  size_t counters, scan_tmp, heavy, dX, dY, dR, dZ, xg, dH, dqkv, dkva, Dq, head_partial, dfilm, dx0, dh, dA, dP, dU,
+  size_t counters, scan_tmp, heavy, dX, dY, dR, dZ, dH, dqkv, dkva, Dq, head_partial, dfilm, dx0, dh, dA, dP, dU,
       colpart, gemm_partial;
   size_t gemm_partial_floats;
-  int chunks;      // 256-row chunks over the graphs (column sums)
+  int chunks;      // kColSumRows-row chunks over the graphs (column sums)
   int64_t s_cap;
 };
 int check_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p);
@@ -108,6 +108,7 @@ constexpr int kAttnQ = 128;         // queries per attention work-group
 // post-attention work-group per compute unit.
 constexpr int kSplitRows = 256 * 128;
 constexpr int kSampleRows = 256;    // nodes per sampling work-group
+constexpr int kColSumRows = 64;     // rows per column-sum chunk of the backward pass
 constexpr int kEvalWindowRows = 64;  // nodes per window of the evaluator
 constexpr int kEvalMinRing = 4096;   // graphs up to this length never need their finish times in memory
 

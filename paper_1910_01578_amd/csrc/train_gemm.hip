@@ -149,6 +149,12 @@ struct Stage {
         for (int i = 0; i < 8; ++i)
           if (gran(u) * 8 + i >= ks) v[u][h][i] = (T)0.f;
   }
+  // the unit's 8 values added up (one unit of one row per thread)
+  __device__ __forceinline__ float sum8() const {
+    static_assert(U == 1 && P == 1, "one row per thread");
+    const T(&a)[8] = v[0][0];
+    return (((float)a[0] + (float)a[1]) + ((float)a[2] + (float)a[3])) + (((float)a[4] + (float)a[5]) + ((float)a[6] + (float)a[7]));
+  }
   __device__ __forceinline__ void store(char* s) const {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -238,7 +244,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
     la[set].load(g.a + (size_t)m0 * g.sam + (size_t)k * g.sak, g.sam, g.sak, g.M - m0, ke - k);
     lb[set].load(g.b + (size_t)n0 * g.sbn + (size_t)k * g.sbk, g.sbn, g.sbk, g.N - n0, ke - k);
   };
+  double rowsum = 0.0;                                   // a weight gradient's bias: the sums of A's rows over k
   auto split = [&](auto set, int buf) {
+    if constexpr (!AKF) rowsum += (double)la[set].sum8();
     la[set].store(lds + buf * kBuf);
     lb[set].store(lds + buf * kBuf + PA * kPlane);
   };
@@ -311,6 +319,20 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
     step(c0, k);
     step(c1, k + KS);
   }
+  if constexpr (!AKF) {
+    if (g.rowsum && n0 == 0) {                           // the k granules of a row, in order
+      double* red = reinterpret_cast<double*>(lds);
+      red[threadIdx.x] = rowsum;
+      __syncthreads();
+      const int m = m0 + (int)threadIdx.x;
+      if (threadIdx.x < BM && m < g.M) {
+        double t = 0.0;
+        for (int q = 0; q < 256 / BM; ++q) t += red[threadIdx.x + q * BM];
+        if (partial) partial[(size_t)gridDim.x / (nt * mt) * g.M * g.N + (size_t)z * g.M + m] = (float)t;
+        else g.rowsum[m] = (float)t;
+      }
+    }
+  }
   // lane: row mw + MT i + col of C, groups of 4 columns
 #pragma unroll
   for (int i = 0; i < NB; ++i)
@@ -342,15 +364,43 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
       }
 }
 
-template <typename TA, typename TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_reduce(GemmStrided<TA, TB> g, int splits, const float* partial) {
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i >= (size_t)g.M * g.N) return;
+// V consecutive elements of C a thread (then, in the last work-groups, one row sum).
+template <typename TA, typename TB, int V>
+__global__ __launch_bounds__(256) void k_gemm_reduce(GemmStrided<TA, TB> g, int splits, const float* partial, int blocks) {
+  const size_t mn = (size_t)g.M * g.N;
+  if ((int)blockIdx.x >= blocks) {
+    const int m = ((int)blockIdx.x - blocks) * 256 + (int)threadIdx.x;
+    if (m >= g.M) return;
+    double t = 0.0;
+    for (int z = 0; z < splits; ++z) t += (double)partial[splits * mn + (size_t)z * g.M + m];
+    g.rowsum[m] = (float)t;
+    return;
+  }
+  const size_t i = (blockIdx.x * (size_t)256 + threadIdx.x) * V;
+  if (i >= mn) return;
   const int m = (int)(i / g.N), n = (int)(i % g.N);
-  double s = 0.0;   // the splits' sums added in double: long reductions (k = rows) keep fp32 accuracy
-  for (int z = 0; z < splits; ++z) s += (double)partial[(size_t)z * g.M * g.N + i];
-  float v[1] = {(float)s};
-  epilogue<EPI, 1>(g, m, n, v);
+  double t[V];   // the splits' sums added in double: long reductions (k = rows) keep fp32 accuracy
+#pragma unroll
+  for (int r = 0; r < V; ++r) t[r] = 0.0;
+  int z = 0;
+  for (; z + 8 <= splits; z += 8) {
+    Pack<float, V> q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const Pack<float, V>*>(partial + (z + u) * mn + i);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int r = 0; r < V; ++r) t[r] += (double)q[u].v[r];
+  }
+  for (; z < splits; ++z) {
+    const Pack<float, V> q = *reinterpret_cast<const Pack<float, V>*>(partial + z * mn + i);
+#pragma unroll
+    for (int r = 0; r < V; ++r) t[r] += (double)q.v[r];
+  }
+  float v[V];
+#pragma unroll
+  for (int r = 0; r < V; ++r) v[r] = (float)t[r];
+  epilogue<E_RAW, V>(g, m, n, v);
 }
 
 namespace {
@@ -409,7 +459,7 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
     constexpr int kMostRows = 2048, kLeastRows = 256;
     if (vec && g.M >= 128 && g.N >= 128) bm = 128;
     const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bm - 1) / bm);
-    const long most = partial ? std::min<long>(std::max(1, g.K / kLeastRows), (long)(partial_floats / ((size_t)g.M * g.N))) : 1;
+    const long most = partial ? std::min<long>(std::max(1, g.K / kLeastRows), std::max<long>(1, (long)(partial_floats / ((size_t)g.M * (g.N + 1))))) : 1;
     double best = 0.0;
     for (long n = partial ? std::min<long>(most, (g.K + kMostRows - 1) / kMostRows) : 1; n <= most; ++n) {
       const double rows = std::max(1.0, std::ceil((double)g.K / n));
@@ -450,16 +500,16 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
     if constexpr (std::is_same<TA, float>::value) {
       switch (epi) {
         GDP_GEMM_CASE(E_RAW, false, false);
-        GDP_GEMM_CASE(E_ACC, false, false);
       }
     }
   }
 #undef GDP_GEMM_CASE
   if (e != hipSuccess || splits == 1) return e;
-  const size_t n = (size_t)g.M * g.N;
-  const dim3 rgrid((unsigned)((n + 255) / 256));
-  if (epi == E_RAW) hipLaunchKernelGGL((k_gemm_reduce<TA, TB, E_RAW>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial);
-  else hipLaunchKernelGGL((k_gemm_reduce<TA, TB, E_ACC>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial);
+  const int v = vec ? 4 : 1;
+  const int blocks = (int)(((size_t)g.M * g.N / v + 255) / 256);
+  const dim3 rgrid((unsigned)(blocks + (g.rowsum ? (g.M + 255) / 256 : 0)));
+  if (vec) hipLaunchKernelGGL((k_gemm_reduce<TA, TB, 4>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial, blocks);
+  else hipLaunchKernelGGL((k_gemm_reduce<TA, TB, 1>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial, blocks);
   return hipGetLastError();
 }
 

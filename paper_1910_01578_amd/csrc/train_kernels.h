@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "device_common.h"
+#include "kernels.h"
 
 namespace gdp {
 namespace tr {
@@ -34,44 +35,57 @@ struct GemmStrided {
   const float* res = nullptr;
   long ldr = 0;
   bool accumulate = false;
+  float* rowsum = nullptr;   // weight gradients (a slow in k): out, [M], sum_k A(m, k)
 };
 // partial: scratch for split-k sums (partial_floats floats; null: no split).
 template <typename TA, typename TB>
 hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, size_t partial_floats, hipStream_t s);
 
-// out[g][c] (+)= sum over graph g's rows of a[r][c] (* b[r][c]); ct holds the
-// graphs and their 256-row chunks (chunks of them); partial: chunks * C floats.
-constexpr int kColChunkRows = 256;
-template <typename TA>
-hipError_t launch_colsum(const TA* a, int lda, const float* b, int ldb, int C, const GraphTable& ct, int chunks,
-                         float* partial, float* out, int ldo, bool accumulate, hipStream_t s);
+// Row-wise kernels take widths of 64, 128 or 256.  Per-graph column sums run over
+// kColChunkRows-row chunks (ct: the graphs and those chunks), added up in order.
+constexpr int kColChunkRows = 64;
 
 template <typename T>
 hipError_t launch_ln_fwd(const float* r, int n, int d, const T* g, const T* b, float* out, hipStream_t s);
-// dr = LayerNorm backward; xg[r][c] = dout * xhat (the gain gradient's terms).
+// LayerNorm backward: dr, and the gain's and shift's gradients.  rows: all rows
+// as one graph; partial: chunks * 2 d floats.
 template <typename T>
-hipError_t launch_ln_bwd(const float* r, const float* dout, int n, int d, const T* g, float* dr, float* xg,
-                         hipStream_t s);
+hipError_t launch_ln_bwd(const float* r, const float* dout, int d, const T* g, const GraphTable& rows, int chunks,
+                         float* dr, float* dg, float* db, float* partial, hipStream_t s);
 
 template <typename TX>
 hipError_t launch_film_apply(const TX* x, int n, int d, const float* gamma, const float* beta, const GraphTable& gt,
                              float* y, hipStream_t s);
-hipError_t launch_film_dx(const float* dy, int n, int d, const float* gamma, const GraphTable& gt, float* dx,
-                          hipStream_t s);
+// FiLM backward: dx = gamma dy, dgamma[g] = sum over graph g of dy x, dbeta[g] =
+// sum of dy.  partial: chunks * 2 d floats.
+hipError_t launch_film_bwd(const float* dy, const float* x, int d, const float* gamma, const GraphTable& ct, int chunks,
+                           float* dx, float* dgamma, float* dbeta, float* partial, hipStream_t s);
+// The FiLM weights' gradients of every layer and the graph embeddings' gradient
+// dx0 [G, H], from dfilm ([L][2][G][d]: dgamma, then dbeta).
+struct FilmWeightGrads {
+  float* wg[kFilmLayersPerLaunch];
+  float* bg[kFilmLayersPerLaunch];
+  float* wb[kFilmLayersPerLaunch];
+  float* bb[kFilmLayersPerLaunch];
+};
+template <typename T>
+hipError_t launch_film_weights_bwd(const FilmLayers<T>& w, const FilmWeightGrads& gr, int layers, const float* dfilm,
+                                   const float* x0, int G, int d, int H, float* dx0, hipStream_t s);
 
-enum Ew { EW_ADD = 0, EW_MASK_POS = 1, EW_SIGMOID_GRAD = 2, EW_SCALE_BY = 3 };
-hipError_t launch_ew(int op, const float* a, const float* b, const float* c, size_t n, float* out, hipStream_t s);
+// out = a where b > 0, else 0 (ReLU').
+hipError_t launch_mask_pos(const float* a, const float* b, size_t n, float* out, hipStream_t s);
 
-// x0[g] = mean of graph g's rows of h; chunks: the graphs with their 256-row chunks (n_chunks of them),
-// partial: n_chunks * H floats.
-hipError_t launch_meanpool_f32(const float* h, int H, const GraphTable& chunks, int n_chunks, float* partial,
-                               float* x0, hipStream_t s);
+// x0[g] = mean of graph g's rows of h; partial: chunks * H floats.
+hipError_t launch_meanpool_f32(const float* h, int H, const GraphTable& ct, int chunks, float* partial, float* x0,
+                               hipStream_t s);
 hipError_t launch_meanpool_bwd(const float* dx0, int n, int H, const GraphTable& gt, float* dh, hipStream_t s);
 
 hipError_t launch_gather_max_arg(const float* P, const int* s_ptr, const int* s_idx, int n, int H, float* A, int* arg,
                                  hipStream_t s);
+// dZ = (the max-pool's backward of dA) P (1 - P): the gradient before the sigmoid.
 hipError_t launch_gather_max_bwd(const float* dA, const int* arg, const int* row_ptr, const int* col_idx,
-                                 const int* in_ptr, const int* in_idx, int n, int H, float* dP, hipStream_t s);
+                                 const int* in_ptr, const int* in_idx, const float* P, int n, int H, float* dZ,
+                                 hipStream_t s);
 hipError_t launch_sort_rows(const int* ptr, int n, int* idx, hipStream_t s);
 
 // qkv [n, 3d] fp32; o [n, d]; lse [n, heads].
@@ -83,9 +97,10 @@ hipError_t launch_attn_bwd(const float* qkv, const float* O, const float* dO, co
                            int heads, int seg, int mem, const GraphTable& gt, float* Dq, float* dqkv_live,
                            float* dkv_all, hipStream_t s);
 
-template <typename T>
-hipError_t launch_adam(float* master, T* param, const float* grad, float* m, float* v, int64_t n, float lr, float b1,
-                       float b2, float eps, float c1, float c2, hipStream_t s);
+// Adam on up to kAdamTensors tensors in one launch.
+constexpr int kAdamTensors = 64;
+hipError_t launch_adam(const gdp_adam_tensor* t, int n_tensors, bool to_bf16, float lr, float b1, float b2, float eps,
+                       float c1, float c2, hipStream_t s);
 
 }  // namespace tr
 }  // namespace gdp
