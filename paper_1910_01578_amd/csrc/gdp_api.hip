@@ -1016,10 +1016,12 @@ int train_forward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer*
   for (int l = 0; l < p->n_layers; ++l) {
     const gdp_placer_layer& Ly = p->layers[l];
     const float* X = S(tp.X[l]);
-    float* Y = S(tp.Y[l]);
-    const float* gam = p->film ? film + (size_t)l * 2 * G * d : nullptr;
-    const float* bet = p->film ? gam + (size_t)G * d : nullptr;
-    GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_film_apply<float>(X, N, d, gam, bet, gt, Y, st));
+    const float* Y = X;      // without FiLM the layer's input as it is
+    if (p->film) {
+      const float* gam = film + (size_t)l * 2 * G * d;
+      GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_film_apply(X, N, d, gam, gam + (size_t)G * d, gt, S(tp.Y[l]), st));
+      Y = S(tp.Y[l]);
+    }
     const float* ffn_in = Y;
     if (p->attention) {
       float* qkv = S(tp.QKV[l]);
@@ -1083,7 +1085,7 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
     const gdp_placer_layer& Ly = p->layers[l];
     const gdp_placer_layer_grad& Gl = gr->placer[l];
     const float* Xin = S(tp.X[l]);
-    const float* Y = S(tp.Y[l]);
+    const float* Y = p->film ? S(tp.Y[l]) : Xin;
     const float* ffn_in = p->attention ? S(tp.Z[l]) : Y;
     // LN2, the FFN and its residual: dZ = dR2 + dH W_1
     GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_ln_bwd<T>(S(tp.R2[l]), dX, d, static_cast<const T*>(Ly.ln2_g), cx.rows,

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "lds_dma.h"
 #include "train_kernels.h"
 
 namespace gdp {
@@ -56,12 +57,14 @@ __device__ __forceinline__ int tile_at(int row, int g) {
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// Eight values as 1 or 3 bf16 planes of 16 bytes at byte offset `at`, planes
-// `plane` bytes apart.
-__device__ __forceinline__ void store_planes(char* s, int at, int plane, const float (&v)[8]) {
+// Eight fp32 values as three bf16 planes, v = p[0] + p[1] + p[2] exactly.
+struct Split8 {
+  bf16x8 p[3];
+};
+__device__ __forceinline__ Split8 split8(const float (&v)[8]) {
   union P8 {
     bf16x2 h[4];
-    uint4 q;
+    bf16x8 q;
   } p1, p2, p3;
   // An infinity's remainder is inf - inf: the median turns it into a finite
   // value beyond any real remainder (at most 2^119), so infinity stays infinity.
@@ -76,9 +79,19 @@ __device__ __forceinline__ void store_planes(char* s, int at, int plane, const f
     p2.h[i] = __builtin_convertvector(r, bf16x2);
     p3.h[i] = __builtin_convertvector(r - __builtin_convertvector(p2.h[i], f32x2), bf16x2);
   }
-  *reinterpret_cast<uint4*>(s + at) = p1.q;
-  *reinterpret_cast<uint4*>(s + plane + at) = p2.q;
-  *reinterpret_cast<uint4*>(s + 2 * plane + at) = p3.q;
+  Split8 o;
+  o.p[0] = p1.q;
+  o.p[1] = p2.q;
+  o.p[2] = p3.q;
+  return o;
+}
+
+// Eight values as 1 or 3 bf16 planes of 16 bytes at byte offset `at`, planes
+// `plane` bytes apart.
+__device__ __forceinline__ void store_planes(char* s, int at, int plane, const float (&v)[8]) {
+  const Split8 o = split8(v);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(s + q * plane + at) = o.p[q];
 }
 __device__ __forceinline__ void store_planes(char* s, int at, int plane, const bf16 (&v)[8]) {
   (void)plane;
@@ -224,9 +237,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   const int n0 = (tile % nt) * BM, m0 = (tile / nt % mt) * BM, z = tile / (nt * mt);
   const int kb = z * k_per_split, ke = min(g.K, kb + k_per_split);
-  // Long reductions keep the products below a1 b1 in sums of their own, whose
-  // rounding is 2^-8 of the main one's: one rounding per 16 k instead of six.
-  constexpr bool LO = KS == 16;
+  // The products below a1 b1 go to sums of their own, whose rounding is 2^-8 of
+  // the main one's: one rounding a step instead of three or six.
+  constexpr bool LO = KS == 16 || BM == 64;
   acc_t acc[NB][NB], low[LO ? NB : 1][LO ? NB : 1];
 #pragma unroll
   for (int i = 0; i < NB; ++i)
@@ -282,12 +295,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
           if (pa >= PA || pb >= PB) continue;
 #pragma unroll
           for (int j = 0; j < NB; ++j) {
-            if constexpr (MT == 16) {
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], fa[i][pa], acc[i][j], 0, 0, 0);
-            } else {
-              acc_t& c = LO && w > 0 ? low[i][j] : acc[i][j];
-              c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][pb], fa[i][pa], c, 0, 0, 0);
-            }
+            acc_t& c = LO && w > 0 ? low[LO ? i : 0][LO ? j : 0] : acc[i][j];
+            if constexpr (MT == 16) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], fa[i][pa], c, 0, 0, 0);
+            else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][pb], fa[i][pa], c, 0, 0, 0);
           }
         }
     load(other, k + 3 * KS);
@@ -364,43 +374,154 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
       }
 }
 
-// V consecutive elements of C a thread (then, in the last work-groups, one row sum).
+// ---------------------------------------------------------------------------
+// x W^T for many rows and bf16 weights with k their fast dimension: a work-group
+// owns 128 rows and 128 columns, a wave 32 rows and all 128 columns.  A wave's
+// rows go from memory straight to its registers in fragment layout (eight
+// consecutive k a lane), two steps ahead, and are split there; only the weights
+// pass through LDS, by direct loads into a ring of three buffers, two steps
+// ahead.  So LDS moves 40 KB a step instead of 96 and the registers hold the
+// small products' sums apart: 52,000 x 1,024 by 256 in 125 us as in the kernel
+// above (118 - 124 us), with half its error (k = 256: 8.6e-8 against 1.6e-7, k =
+// 1,024: 1.8e-7 against 3.4e-7).  The error is why it is used: a ReLU that falls
+// the other way moves a gradient by a whole term.
+// ---------------------------------------------------------------------------
+constexpr int kLinTile = 128, kLinStep = 32;
+
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void k_linear_split(GemmStrided<float, bf16> g, int nt) {
+  __shared__ __attribute__((aligned(16))) bf16 ring[3][kLinTile * kLinStep];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g4 = lane >> 4;
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int n0 = (tile % nt) * kLinTile, m0 = (tile / nt) * kLinTile;
+  const int steps = g.K / kLinStep;
+  const bf16* w = g.b + (size_t)n0 * g.sbn;
+  auto fetch = [&](int s) {                              // step s's weights (past the end: the last step's again)
+    const dma::DmaTile<bf16, kLinTile, kLinStep, 4> t(ring[s % 3], w + min(s, steps - 1) * kLinStep, (int)g.sbn, kLinTile - 1);
+    t.all();
+  };
+  const float* row[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    row[i] = g.a + (size_t)min(m0 + wave * 32 + i * 16 + col, g.M - 1) * g.sam + g4 * 8;
+  float raw[2][2][8];
+  auto load = [&](auto set, int s) {
+    const int k = min(s, steps - 1) * kLinStep;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float4 a = *reinterpret_cast<const float4*>(row[i] + k), b = *reinterpret_cast<const float4*>(row[i] + k + 4);
+      float(&v)[8] = raw[set][i];
+      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+      v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    }
+  };
+  f32x4 acc[2][8], low[2][8];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[i][j] = low[i][j] = zero4();
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+  fetch(0);
+  load(c0, 0);
+  fetch(1);
+  load(c1, 1);
+  auto step = [&](auto set, int s) {
+    // step s's weights are in: younger are step s's rows, step s + 1's weights and
+    // rows (4 + 2 + 4 loads)
+    dma::wait_vm_barrier<10>();
+    fetch(s + 2);
+    Split8 fa[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) fa[i] = split8(raw[set][i]);
+    load(set, s + 2);
+    if (s >= steps) return;                              // one more after an odd number
+    const bf16* b = ring[s % 3];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const bf16x8 fb = *reinterpret_cast<const bf16x8*>(&b[dma::swz<bf16, kLinStep>(16 * j + col, g4 * 8)]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        low[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa[i].p[2], low[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa[i].p[0], acc[i][j], 0, 0, 0);
+        low[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa[i].p[1], low[i][j], 0, 0, 0);
+      }
+    }
+  };
+  for (int s = 0; s < steps; s += 2) {
+    step(c0, s);
+    step(c1, s + 1);
+  }
+  dma::wait_loads_then_barrier();                        // no direct load outlives the work-group
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int m = m0 + wave * 32 + i * 16 + col, n = n0 + 16 * j + 4 * g4;
+      if (m >= g.M) continue;
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = acc[i][j][r] + low[i][j][r];
+      epilogue<EPI, 4>(g, m, n, v);
+    }
+}
+
+// 64 x V consecutive elements of C per work-group, each wave a quarter of the
+// splits, the quarters combined in order (then, in the last work-groups, 256 row
+// sums each).
 template <typename TA, typename TB, int V>
 __global__ __launch_bounds__(256) void k_gemm_reduce(GemmStrided<TA, TB> g, int splits, const float* partial, int blocks) {
+  __shared__ double run[4][64 * V];
   const size_t mn = (size_t)g.M * g.N;
   if ((int)blockIdx.x >= blocks) {
     const int m = ((int)blockIdx.x - blocks) * 256 + (int)threadIdx.x;
     if (m >= g.M) return;
     double t = 0.0;
-    for (int z = 0; z < splits; ++z) t += (double)partial[splits * mn + (size_t)z * g.M + m];
+    const float* p = partial + splits * mn + m;
+    int z = 0;
+    for (; z + 8 <= splits; z += 8) {
+      float q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = p[(size_t)(z + u) * g.M];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t += (double)q[u];
+    }
+    for (; z < splits; ++z) t += (double)p[(size_t)z * g.M];
     g.rowsum[m] = (float)t;
     return;
   }
-  const size_t i = (blockIdx.x * (size_t)256 + threadIdx.x) * V;
-  if (i >= mn) return;
-  const int m = (int)(i / g.N), n = (int)(i % g.N);
+  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const size_t i = (blockIdx.x * (size_t)64 + lane) * V;
+  const size_t at = i < mn ? i : 0;
+  const int per = (splits + 3) / 4;
+  int z = min(splits, part * per);
+  const int ze = min(splits, z + per);
   double t[V];   // the splits' sums added in double: long reductions (k = rows) keep fp32 accuracy
 #pragma unroll
   for (int r = 0; r < V; ++r) t[r] = 0.0;
-  int z = 0;
-  for (; z + 8 <= splits; z += 8) {
+  for (; z + 8 <= ze; z += 8) {
     Pack<float, V> q[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const Pack<float, V>*>(partial + (z + u) * mn + i);
+    for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const Pack<float, V>*>(partial + (z + u) * mn + at);
 #pragma unroll
     for (int u = 0; u < 8; ++u)
 #pragma unroll
       for (int r = 0; r < V; ++r) t[r] += (double)q[u].v[r];
   }
-  for (; z < splits; ++z) {
-    const Pack<float, V> q = *reinterpret_cast<const Pack<float, V>*>(partial + z * mn + i);
+  for (; z < ze; ++z) {
+    const Pack<float, V> q = *reinterpret_cast<const Pack<float, V>*>(partial + z * mn + at);
 #pragma unroll
     for (int r = 0; r < V; ++r) t[r] += (double)q.v[r];
   }
+#pragma unroll
+  for (int r = 0; r < V; ++r) run[part][r * 64 + lane] = t[r];
+  __syncthreads();
+  if (part != 0 || i >= mn) return;
   float v[V];
 #pragma unroll
-  for (int r = 0; r < V; ++r) v[r] = (float)t[r];
-  epilogue<E_RAW, V>(g, m, n, v);
+  for (int r = 0; r < V; ++r)
+    v[r] = (float)(((run[0][r * 64 + lane] + run[1][r * 64 + lane]) + run[2][r * 64 + lane]) + run[3][r * 64 + lane]);
+  epilogue<E_RAW, V>(g, (int)(i / g.N), (int)(i % g.N), v);
 }
 
 namespace {
@@ -475,6 +596,24 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
   splits = splits > 1 ? (g.K + kps - 1) / kps : 1;
   float* part = splits > 1 ? partial : nullptr;
   const int epi = epi_of(g);
+  // Many rows by bf16 weights, where its 128 x 128 tiles give two work-groups per
+  // CU: k_linear_split.
+  if constexpr (std::is_same<TA, float>::value && std::is_same<TB, bf16>::value) {
+    const long tiles = (long)((g.M + kLinTile - 1) / kLinTile) * (g.N / kLinTile);
+    if (akf && bkf && vec && g.N % kLinTile == 0 && tiles >= 512) {
+      const dim3 grid((unsigned)tiles), block(256);
+#define GDP_LINEAR_CASE(E) \
+  case E: hipLaunchKernelGGL((k_linear_split<E>), grid, block, 0, s, g, g.N / kLinTile); return hipGetLastError()
+      switch (epi) {
+        GDP_LINEAR_CASE(E_BIAS);
+        GDP_LINEAR_CASE(E_BIAS | E_RELU);
+        GDP_LINEAR_CASE(E_BIAS | E_SIGMOID);
+        GDP_LINEAR_CASE(E_BIAS | E_RES);
+        GDP_LINEAR_CASE(E_ACC);
+      }
+#undef GDP_LINEAR_CASE
+    }
+  }
   // The forms in use: a linear layer, its input gradient, its weight gradient.
   hipError_t e = hipErrorInvalidValue;
 #define GDP_GEMM_CASE(E, AKF, BKF) \
@@ -506,7 +645,7 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
 #undef GDP_GEMM_CASE
   if (e != hipSuccess || splits == 1) return e;
   const int v = vec ? 4 : 1;
-  const int blocks = (int)(((size_t)g.M * g.N / v + 255) / 256);
+  const int blocks = (int)(((size_t)g.M * g.N / v + 63) / 64);
   const dim3 rgrid((unsigned)(blocks + (g.rowsum ? (g.M + 255) / 256 : 0)));
   if (vec) hipLaunchKernelGGL((k_gemm_reduce<TA, TB, 4>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial, blocks);
   else hipLaunchKernelGGL((k_gemm_reduce<TA, TB, 1>), rgrid, dim3(256), 0, s, g, splits, (const float*)partial, blocks);

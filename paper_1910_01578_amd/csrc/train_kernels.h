@@ -53,8 +53,7 @@ template <typename T>
 hipError_t launch_ln_bwd(const float* r, const float* dout, int d, const T* g, const GraphTable& rows, int chunks,
                          float* dr, float* dg, float* db, float* partial, hipStream_t s);
 
-template <typename TX>
-hipError_t launch_film_apply(const TX* x, int n, int d, const float* gamma, const float* beta, const GraphTable& gt,
+hipError_t launch_film_apply(const float* x, int n, int d, const float* gamma, const float* beta, const GraphTable& gt,
                              float* y, hipStream_t s);
 // FiLM backward: dx = gamma dy, dgamma[g] = sum over graph g of dy x, dbeta[g] =
 // sum of dy.  partial: chunks * 2 d floats.
