@@ -231,3 +231,28 @@ def test_directional_derivative_full_size_fp32():
         p.copy_(b)
     _log(f"directional derivative: central differences {[f'{f:.6e}' for f in fds]}  |g|^2 {gnorm ** 2:.6e}")
     assert abs(fds[-1] - gnorm ** 2) <= 0.02 * gnorm ** 2
+
+
+# One graph size or head layout a branch of the products' and the attention's
+# dispatch: rows one past a tile, products of many rows with a ragged last tile
+# (d_ff = 1,024: 8 column tiles, so 8,193 rows take the direct-to-register
+# kernel), odd output widths (scalar loads), each head size with one and two
+# columns a lane, memories longer than and unaligned to the segments.
+KERNEL_PATHS = [
+    ("tile_plus_1_odd_devices", "bf16", dict(graph_sizes=(129,), hidden=128, heads=4, n_devices=7)),
+    ("many_rows_ragged", "bf16", dict(graph_sizes=(8193,), hidden=128, heads=4, d_ff=1024, seg_len=512, mem_len=100)),
+    ("many_rows_f32", "f32", dict(graph_sizes=(8193,), hidden=128, heads=8, d_ff=1024, seg_len=128, mem_len=128)),
+    ("dh16_two_columns", "f32", dict(graph_sizes=(700, 65, 1, 127), hidden=64, heads=4, seg_len=128, mem_len=200)),
+    ("dh16_one_column", "bf16", dict(graph_sizes=(300, 64), hidden=128, heads=8, seg_len=72, mem_len=33)),
+    ("dh32_two_columns", "bf16", dict(graph_sizes=(1100, 3), hidden=128, heads=4, seg_len=520, mem_len=600)),
+    ("dh64_ragged", "f32", dict(graph_sizes=(333, 65), hidden=256, heads=4, seg_len=128, mem_len=128)),
+]
+
+
+@pytest.mark.parametrize("label,dtype,over", KERNEL_PATHS, ids=[k[0] for k in KERNEL_PATHS])
+def test_backward_parity_kernel_paths(label, dtype, over):
+    cfg = W.get_config("tiny_layered_256").replace(dtype=dtype, **over)
+    g, w = W.make_graph(cfg), W.make_weights(cfg)
+    _log("backward kernel path", label)
+    t, ref, att, fl = _run(cfg, g, w, seed=3)
+    _compare_grads(t, ref, cfg, att, fl)
