@@ -23,8 +23,15 @@
 //
 // What bounds it: the vector ALU (exponentials, splits) and the matrix
 // instructions together.  52,000 rows, 8 heads of 32, segments and memory of 512
-// (16x16x4 fp32 instructions before): forward 597 -> 360 us, dQ 853 -> 430 us,
-// dK and dV 1,554 -> 650 us.
+// (16x16x4 fp32 instructions before): forward 597 -> 305 us, dQ 853 -> 373 us,
+// dK and dV 1,554 -> 580 us.
+//
+// The gradients of W_q and W_k are small differences of large sums (a row's ds
+// add up to zero), so what the forward divides by and sums has to agree with what
+// the backward forms: the denominators are summed as trees, O and dQ add each 32
+// rows in one rounding, the log-sum-exp stays in log2 units.  Error of these two
+// gradients against float64 with the forward's own ReLU signs, d_h = 32, 6,000
+// nodes: 2.0e-4 without these, 9.7e-5 with them (fp32 instructions: 1.3e-4).
 #include <algorithm>
 #include <type_traits>
 
@@ -39,7 +46,6 @@ namespace {
 
 constexpr int kAttnTile = 64;    // rows staged per tile
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -164,7 +170,10 @@ struct Tile {
 
 // A lane's operand for products over the head dimension: its own row's DH
 // values, 8 per lane group and k step.  With DH = 16 one instruction covers two
-// plane pairs: lane groups 0, 1 hold one plane's 16 values, groups 2, 3 another's.
+// plane pairs: lane groups 0, 1 hold one plane's 16 values, groups 2, 3 another's;
+// the two largest products have an instruction each (twice one half), as smaller
+// ones beside them would lose their last bits (gradients of W_q and W_k 1.6e-4 ->
+// 7e-5, 4,000 nodes; a fourth instruction, 2.5 % of that update).
 template <int DH>
 struct RowOperand {
   static constexpr int NK = DH == 64 ? 2 : 1;
@@ -182,12 +191,11 @@ struct RowOperand {
       }
       k[s] = split8<true>(t);
     }
-    if constexpr (DH == 16) {      // B planes of the pairs (a3 b1 | a1 b3), (a2 b2 | a2 b1), (a1 b2 | a1 b1)
+    if constexpr (DH == 16) {      // B planes of the pairs (a3 b1 | a1 b3), (a2 b2 | a1 b2) and (a b1/2 | a b1/2)
       const Planes o = k[0];
-      const bool up = g4 >= 2;
-      k[0].p[0] = up ? o.p[2] : o.p[0];
-      k[0].p[1] = up ? o.p[0] : o.p[1];
-      k[0].p[2] = k[0].p[1];
+      k[0].p[0] = g4 >= 2 ? o.p[2] : o.p[0];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) k[0].p[2][i] = (bf16)((float)o.p[0][i] * 0.5f);
     }
   }
 };
@@ -201,12 +209,13 @@ __device__ __forceinline__ void dot_rows(f32x4 (&acc)[COLS], const char* tile, i
   for (int c = 0; c < COLS; ++c) acc[c] = zero4();
   if constexpr (DH == 16) {
     const bool up = g4 >= 2;
-    const bf16x8 a31 = T::granule(tile, up ? 0 : 2, row0 + col, g4 & 1), a2 = T::granule(tile, 1, row0 + col, g4 & 1),
-                 a1 = T::granule(tile, 0, row0 + col, g4 & 1);
+    const bf16x8 a31 = T::granule(tile, up ? 0 : 2, row0 + col, g4 & 1), a21 = T::granule(tile, up ? 0 : 1, row0 + col, g4 & 1),
+                 a2 = T::granule(tile, 1, row0 + col, g4 & 1), a1 = T::granule(tile, 0, row0 + col, g4 & 1);
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
       acc[c] = mma(a31, y[c].k[0].p[0], acc[c]);
-      acc[c] = mma(a2, y[c].k[0].p[1], acc[c]);
+      acc[c] = mma(a21, y[c].k[0].p[1], acc[c]);
+      acc[c] = mma(a2, y[c].k[0].p[2], acc[c]);
       acc[c] = mma(a1, y[c].k[0].p[2], acc[c]);
     }
   } else {
@@ -223,8 +232,9 @@ __device__ __forceinline__ void dot_rows(f32x4 (&acc)[COLS], const char* tile, i
 
 // out[db][c] (head dims 16 db .., column) += tile^T . w over the tile's rows
 // [row0, row0 + 32); w[c]: the lane's values of rows row0 + 4 g4 + i and row0 +
-// 16 + 4 g4 + i.
-template <int DH, int COLS>
+// 16 + 4 g4 + i.  APART: the 32 rows are summed from zero and added by the vector
+// ALU, one rounding of the running sum instead of six.
+template <bool APART, int DH, int COLS>
 __device__ __forceinline__ void acc_rows(f32x4 (&out)[DH / 16][COLS], const char* tile, int row0, const Planes (&w)[COLS],
                                          int col, int g4) {
   using T = Tile<DH>;
@@ -239,7 +249,15 @@ __device__ __forceinline__ void acc_rows(f32x4 (&out)[DH / 16][COLS], const char
       a.p[q] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
 #pragma unroll
-    for (int c = 0; c < COLS; ++c) out[db][c] = mma6(a, w[c], out[db][c]);
+    for (int c = 0; c < COLS; ++c) {
+      if constexpr (APART) {
+        const f32x4 t = mma6(a, w[c], zero4());
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[db][c][r] += t[r];
+      } else {
+        out[db][c] = mma6(a, w[c], out[db][c]);
+      }
+    }
   }
 }
 
@@ -334,18 +352,18 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
           const float mn = fmaxf(m[c], tmax);
           const float corr = exp2_fast(m[c] - mn);
           m[c] = mn;
-          lsum[c] *= corr;
 #pragma unroll
           for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 4; ++r) oacc[db][c][r] *= corr;
+          float sum[4];
 #pragma unroll
-          for (int kb = 0; kb < 4; ++kb)
+          for (int kb = 0; kb < 4; ++kb) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              s[kb][c][r] = exp2_fast(s[kb][c][r] - mn);
-              lsum[c] += s[kb][c][r];
-            }
+            for (int r = 0; r < 4; ++r) s[kb][c][r] = exp2_fast(s[kb][c][r] - mn);
+            sum[kb] = (s[kb][c][0] + s[kb][c][1]) + (s[kb][c][2] + s[kb][c][3]);
+          }
+          lsum[c] = lsum[c] * corr + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -360,7 +378,7 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
             }
             p[c] = split8<false>(t);
           }
-          acc_rows<DH, COLS>(oacc, sV, 32 * h, p, col, g4);
+          acc_rows<true, DH, COLS>(oacc, sV, 32 * h, p, col, g4);
         }
       });
 #pragma unroll
@@ -373,11 +391,11 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
     for (int db = 0; db < DB; ++db)
       *reinterpret_cast<float4*>(o + (size_t)q[c] * d + c0 + db * 16 + 4 * g4) =
           make_float4(oacc[db][c][0] * inv, oacc[db][c][1] * inv, oacc[db][c][2] * inv, oacc[db][c][3] * inv);
-    if (g4 == 0) lse[(size_t)q[c] * heads + head] = (m[c] + log2f(lsum[c])) * kLn2;
+    if (g4 == 0) lse[(size_t)q[c] * heads + head] = m[c] + log2f(lsum[c]);
   }
 }
 
-// dQ for the work-group's queries: p = exp(s - lse), ds = p (dO . v - Dq),
+// dQ for the work-group's queries: p = exp(s - lse) (lse in log2 units), ds = p (dO . v - Dq),
 // dq = scale * sum_j ds_j k_j (into the Q columns of dqkv, row stride lddq).
 template <int DH, int COLS>
 __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ dO,
@@ -402,7 +420,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__
     const bool ok = q[c] < b.r1;
     qf[c].load(qkv, ld, q[c], ok, c0, g4, scale * kLog2e);
     df[c].load(dO, d, q[c], ok, c0, g4, 1.0f);
-    L2[c] = ok ? lse[(size_t)q[c] * heads + head] * kLog2e : 0.f;
+    L2[c] = ok ? lse[(size_t)q[c] * heads + head] : 0.f;
     Dv[c] = ok ? Dq[(size_t)q[c] * heads + head] : 0.f;
 #pragma unroll
     for (int db = 0; db < DB; ++db) dq[db][c] = zero4();
@@ -436,7 +454,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__
             Planes w[COLS];
 #pragma unroll
             for (int c = 0; c < COLS; ++c) w[c] = split8<false>(t[c]);
-            acc_rows<DH, COLS>(dq, sK, 32 * h, w, col, g4);
+            acc_rows<true, DH, COLS>(dq, sK, 32 * h, w, col, g4);
           }
         };
         if (left >= kAttnTile) tile(std::false_type());
@@ -511,10 +529,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
   // lse (waves 0, 2) and Dq (waves 1, 3) of a tile's queries, one value per lane
   float aux = 0.f;
   const float* aux_src = (wave & 1) ? Dq : lse;
-  const float aux_mul = (wave & 1) ? 1.0f : kLog2e;
   auto aux_load = [&](int i) {
     const int sg1 = min(seg_of(i) + seg, b.ge);
-    aux = aux_src[(size_t)min(row_of(i) + lane, sg1 - 1) * heads + head] * aux_mul;
+    aux = aux_src[(size_t)min(row_of(i) + lane, sg1 - 1) * heads + head];
   };
   auto aux_store = [&](int buf) { ((wave & 1) ? sDq[buf] : sL[buf])[lane] = aux; };
   aux_load(0);
@@ -560,10 +577,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
             Planes w[COLS];
 #pragma unroll
             for (int c = 0; c < COLS; ++c) w[c] = split8<false>(p[c]);
-            acc_rows<DH, COLS>(dv, sD, 32 * h, w, col, g4);
+            acc_rows<false, DH, COLS>(dv, sD, 32 * h, w, col, g4);
 #pragma unroll
             for (int c = 0; c < COLS; ++c) w[c] = split8<false>(ds[c]);
-            acc_rows<DH, COLS>(dk, sQ, 32 * h, w, col, g4);
+            acc_rows<false, DH, COLS>(dk, sQ, 32 * h, w, col, g4);
           }
         };
         if (t0 + kAttnTile <= sg1 && (i < own || b.r0 >= sg0 - mem)) tile(std::false_type());
@@ -581,17 +598,17 @@ __global__ void k_attn_dq_rowdot(const float* __restrict__ dO, const float* __re
   const size_t total = (size_t)n * heads;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
     const size_t base = (i / heads) * d + (i % heads) * DH;
-    float s = 0.f;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < DH; t += 4) {
       const float4 a = *reinterpret_cast<const float4*>(dO + base + t);
       const float4 c = *reinterpret_cast<const float4*>(O + base + t);
-      s = fmaf(a.x, c.x, s);
-      s = fmaf(a.y, c.y, s);
-      s = fmaf(a.z, c.z, s);
-      s = fmaf(a.w, c.w, s);
+      s[0] = fmaf(a.x, c.x, s[0]);
+      s[1] = fmaf(a.y, c.y, s[1]);
+      s[2] = fmaf(a.z, c.z, s[2]);
+      s[3] = fmaf(a.w, c.w, s[3]);
     }
-    Dq[i] = s;
+    Dq[i] = (s[0] + s[1]) + (s[2] + s[3]);
   }
 }
 

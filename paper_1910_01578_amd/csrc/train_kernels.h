@@ -87,7 +87,7 @@ hipError_t launch_gather_max_bwd(const float* dA, const int* arg, const int* row
                                  hipStream_t s);
 hipError_t launch_sort_rows(const int* ptr, int n, int* idx, hipStream_t s);
 
-// qkv [n, 3d] fp32; o [n, d]; lse [n, heads].
+// qkv [n, 3d] fp32; o [n, d]; lse [n, heads] in log2 units.
 hipError_t launch_attn_fwd(const float* qkv, int n, int d, int heads, int seg, int mem, const GraphTable& gt,
                            float* o, float* lse, hipStream_t s);
 // dqkv_live [n, 3d]: dQ and the own-segment dK, dV; dkv_all [n, 2d]: those dK,
