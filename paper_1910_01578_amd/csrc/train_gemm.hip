@@ -10,17 +10,24 @@
 // bf16 instructions do 16 times the work of the fp32 ones per cycle, so three
 // products cost 3/16 and six 3/8 of the fp32 instructions.
 //
+// The products below a1 b1 go to sums of their own.  Where an instruction's sum
+// and its products differ much in size, the low bits of the smaller are dropped
+// towards minus infinity: with all products on one sum a result leans by 1e-8 of
+// its root mean square (k = 256, normal operands; apart: 1e-10).  A gradient adds
+// up such results over all rows, and the lean with them: at 52,000 rows column
+// sums were off by 1.6e-6 (three products) and 3.1e-6 (six), apart 9e-8 (fp32
+// instructions 2.8e-7).
+//
 // A work-group (4 waves, 2 x 2) owns a BM x BM tile of C, each wave a (BM/2)^2
 // block.  k advances in steps of KS through two LDS buffers: while a wave's
 // matrix instructions work on step s from one, its vector ALU splits step s + 1
 // into bf16 planes for the other, and the loads of step s + 3 go out into the
 // registers that frees (the memory's latency is two steps).  One barrier a step.
-// KS is 32 (16x16x32 instructions) where k is the operands' fast dimension and
-// 16 (32x32x16; half the LDS, three work-groups a CU) for weight gradients,
-// whose k is the row.  Planes are [row][KS k]; the 16-byte granules of a row are
-// permuted so that eight consecutive rows of a fragment read fall in distinct
-// granules modulo 128 bytes.  Products are formed transposed, so a lane holds 4
-// consecutive n of one m.  With splits > 1 each split of k writes its raw sums
+// KS is 32 (16x16x32 instructions) for 64 x 64 tiles and 16 (32x32x16; half the
+// LDS, and registers for both sums) for 128 x 128 ones.  Planes are [row][KS k];
+// the 16-byte granules of a row are permuted so that eight consecutive rows of a
+// fragment read fall in distinct granules modulo 128 bytes.  Products are formed
+// transposed, so a lane holds 4 consecutive n of one m.  With splits > 1 each split of k writes its raw sums
 // to partial[z]; k_gemm_reduce adds them in split order, in double, and applies
 // the epilogue.
 //
@@ -236,7 +243,7 @@ __device__ __forceinline__ void epilogue(const GemmStrided<TA, TB>& g, int m, in
 template <typename TA, typename TB, int BM, bool AKF, bool BKF, bool VEC, int EPI>
 __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, int k_per_split, float* partial, int nt,
                                                     int mt) {
-  constexpr int KS = AKF || BM == 64 ? 32 : 16;
+  constexpr int KS = BM == 64 ? 32 : 16;
   constexpr int MT = KS == 32 ? 16 : 32;                 // rows and columns of one matrix instruction
   constexpr int WT = BM / 2, NB = WT / MT, PA = planes<TA>(), PB = planes<TB>();
   constexpr int kPlane = BM * KS * 2, kBuf = (PA + PB) * kPlane;
@@ -248,19 +255,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   const int n0 = (tile % nt) * BM, m0 = (tile / nt % mt) * BM, z = tile / (nt * mt);
   const int kb = z * k_per_split, ke = min(g.K, kb + k_per_split);
-  // The products below a1 b1 go to sums of their own, whose rounding is 2^-8 of
-  // the main one's: one rounding a step instead of three or six.
-  constexpr bool LO = KS == 16 || BM == 64;
-  acc_t acc[NB][NB], low[LO ? NB : 1][LO ? NB : 1];
+  acc_t acc[NB][NB], low[NB][NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < MT * MT / 64; ++r) {
-        acc[i][j][r] = 0.f;
-        if constexpr (LO) low[i][j][r] = 0.f;
-      }
+      for (int r = 0; r < MT * MT / 64; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
   Stage<TA, BM, KS, AKF, VEC> la[2];
   Stage<TB, BM, KS, BKF, VEC> lb[2];
   auto load = [&](auto set, int k) {                     // past the end: the last step again
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
           if (pa >= PA || pb >= PB) continue;
 #pragma unroll
           for (int j = 0; j < NB; ++j) {
-            acc_t& c = LO && w > 0 ? low[LO ? i : 0][LO ? j : 0] : acc[i][j];
+            acc_t& c = w > 0 ? low[i][j] : acc[i][j];
             if constexpr (MT == 16) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], fa[i][pa], c, 0, 0, 0);
             else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][pb], fa[i][pa], c, 0, 0, 0);
           }
@@ -376,10 +377,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
         const int m = row_of(i), n = col_of(j, q);
         if (m >= g.M || n >= g.N) continue;
         float v[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        if constexpr (LO) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] += low[i][j][4 * q + r];
-        }
+        for (int r = 0; r < 4; ++r) v[r] += low[i][j][4 * q + r];
         float* o = partial + ((size_t)z * g.M + m) * g.N + n;
         if constexpr (VEC) {
           if (partial) *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);

@@ -256,3 +256,52 @@ def test_backward_parity_kernel_paths(label, dtype, over):
     _log("backward kernel path", label)
     t, ref, att, fl = _run(cfg, g, w, seed=3)
     _compare_grads(t, ref, cfg, att, fl)
+
+
+def _gradients(t, dl):
+    import torch
+    t.backward(torch.from_numpy(dl).cuda())
+    torch.cuda.synchronize()
+    d = t.policy.cfg.hidden
+    out = {}
+    for part, layers in (("gnn", t.grad_gnn), ("placer", t.grad_placer), ("head", [t.grad_head])):
+        for l, lg in enumerate(layers):
+            for k, v in lg.items():
+                if k.endswith("_qkv"):
+                    out.update({f"{part}[{l}].{k[0]}_{q}": to_np(v[i * d:(i + 1) * d]) for i, q in enumerate("qkv")})
+                else:
+                    out[f"{part}[{l}].{k}"] = to_np(v)
+    return out
+
+
+def _opposed(dtype, **over):
+    """Two copies of one graph with gradients dL/dlogits of opposite sign.  Every
+    row of one copy is then the other's negative, and every weight's gradient
+    their sum: 0 where each operation rounds both ways alike.  The norms of those
+    gradients, by the norms under independent gradients of the same size."""
+    cfg = W.get_config("tiny_layered_256").replace(dtype=dtype, **over)
+    one, w = W.make_graph(cfg), W.make_weights(cfg)
+    n, e = one.n_nodes, one.n_edges
+    g = W.graph_from_arrays(cfg, [0, n, 2 * n], np.concatenate([one.row_ptr, one.row_ptr[1:] + e]),
+                            np.concatenate([one.col_idx, one.col_idx + n]), np.concatenate([one.x, one.x]))
+    t = _trainer(cfg, g, w)
+    logits, _ = t.forward()
+    assert bool((logits[:n] == logits[n:]).all())
+    dl = (np.random.default_rng(8).normal(size=(2 * n, cfg.n_devices)) / np.sqrt(n)).astype(np.float32)
+    free = _gradients(t, dl)
+    opposed = _gradients(t, np.concatenate([dl[:n], -dl[:n]]))
+    return {k: float(np.linalg.norm(opposed[k].astype(np.float64)) / np.linalg.norm(free[k].astype(np.float64)))
+            for k in free}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_products_round_both_ways_alike(dtype):
+    """The last layer's gradients behind the head: dH = dR W_2 and dZ = dH W_1 over
+    16,386 rows in 128 x 128 tiles.  A result that leans by r of its root mean
+    square appears as r sqrt(16,386) = 128 r: 4e-7 to 1e-6 for the 3e-9 to 8e-9 of
+    products with all planes on one sum, against the rounding of the sums over
+    rows, 3e-8 for columns and 1e-7 for w_1 (16 rows an instruction)."""
+    err = _opposed(dtype, graph_sizes=(8193,), hidden=128, heads=4, d_ff=1024, seg_len=128, mem_len=128)
+    got = {k: err[f"placer[1].{k}"] for k in ("b_o", "ln1_g", "ln1_b", "w_1", "b_1", "b_2", "ln2_g", "ln2_b")}
+    _log("  opposed gradients", {k: f"{v:.1e}" for k, v in got.items()})
+    assert max(got.values()) <= 2e-7, got
