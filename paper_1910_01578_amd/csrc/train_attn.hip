@@ -32,6 +32,14 @@
 // rows in one rounding, the log-sum-exp stays in log2 units.  Error of these two
 // gradients against float64 with the forward's own ReLU signs, d_h = 32, 6,000
 // nodes: 2.0e-4 without these, 9.7e-5 with them (fp32 instructions: 1.3e-4).
+//
+// For the same reason the backward keeps a1 b1 on a sum of its own (dO . v, dQ, dK,
+// dV): an instruction drops the low bits of what is small beside its sum towards
+// minus infinity, dO . v then leans against Dq in every row alike, and the rows'
+// sums keep that.  Same error at 52,000 nodes, last layer: 6.5e-5 with all pairs on
+// one sum, 5.6e-6 so (fp32 instructions: 6.1e-6); backward of 6 layers 15.1 -> 15.6
+// ms.  The forward's scores and their copies in the backward lean alike for all
+// keys of a query, which the softmax cancels.
 #include <algorithm>
 #include <type_traits>
 
@@ -107,14 +115,19 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// c += a b from the six plane pairs, smallest first.
-__device__ __forceinline__ f32x4 mma6(const Planes& a, const Planes& b, f32x4 c) {
+// c += the five plane pairs of a b below a1 b1, smallest first.
+__device__ __forceinline__ f32x4 mma_low(const Planes& a, const Planes& b, f32x4 c) {
   c = mma(a.p[2], b.p[0], c);
   c = mma(a.p[1], b.p[1], c);
   c = mma(a.p[0], b.p[2], c);
   c = mma(a.p[1], b.p[0], c);
-  c = mma(a.p[0], b.p[1], c);
-  return mma(a.p[0], b.p[0], c);
+  return mma(a.p[0], b.p[1], c);
+}
+__device__ __forceinline__ f32x4 mma_top(const Planes& a, const Planes& b, f32x4 c) { return mma(a.p[0], b.p[0], c); }
+__device__ __forceinline__ f32x4 add4(f32x4 a, f32x4 b) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) a[r] += b[r];
+  return a;
 }
 
 // ds_read_b64_tr_b16: within each group of 16 lanes, destination lane 4q + p
@@ -201,22 +214,24 @@ struct RowOperand {
 };
 
 // acc[c] = tile rows [row0, row0 + 16) . the columns' rows, over the head dimension.
-template <int DH, int COLS>
+// APART: a1 b1 on a sum of its own.
+template <bool APART, int DH, int COLS>
 __device__ __forceinline__ void dot_rows(f32x4 (&acc)[COLS], const char* tile, int row0, const RowOperand<DH> (&y)[COLS],
                                          int col, int g4) {
   using T = Tile<DH>;
+  f32x4 low[COLS];
 #pragma unroll
-  for (int c = 0; c < COLS; ++c) acc[c] = zero4();
+  for (int c = 0; c < COLS; ++c) acc[c] = low[c] = zero4();
   if constexpr (DH == 16) {
     const bool up = g4 >= 2;
     const bf16x8 a31 = T::granule(tile, up ? 0 : 2, row0 + col, g4 & 1), a21 = T::granule(tile, up ? 0 : 1, row0 + col, g4 & 1),
                  a2 = T::granule(tile, 1, row0 + col, g4 & 1), a1 = T::granule(tile, 0, row0 + col, g4 & 1);
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
-      acc[c] = mma(a31, y[c].k[0].p[0], acc[c]);
-      acc[c] = mma(a21, y[c].k[0].p[1], acc[c]);
-      acc[c] = mma(a2, y[c].k[0].p[2], acc[c]);
-      acc[c] = mma(a1, y[c].k[0].p[2], acc[c]);
+      low[c] = mma(a31, y[c].k[0].p[0], low[c]);
+      low[c] = mma(a21, y[c].k[0].p[1], low[c]);
+      low[c] = mma(a2, y[c].k[0].p[2], low[c]);
+      acc[c] = mma(a1, y[c].k[0].p[2], APART ? acc[c] : low[c]);
     }
   } else {
 #pragma unroll
@@ -225,18 +240,27 @@ __device__ __forceinline__ void dot_rows(f32x4 (&acc)[COLS], const char* tile, i
 #pragma unroll
       for (int q = 0; q < 3; ++q) a.p[q] = T::granule(tile, q, row0 + col, s * 4 + g4);
 #pragma unroll
-      for (int c = 0; c < COLS; ++c) acc[c] = mma6(a, y[c].k[s], acc[c]);
+      for (int c = 0; c < COLS; ++c) {
+        if constexpr (APART) {
+          low[c] = mma_low(a, y[c].k[s], low[c]);
+          acc[c] = mma_top(a, y[c].k[s], acc[c]);
+        } else {
+          acc[c] = mma_top(a, y[c].k[s], mma_low(a, y[c].k[s], acc[c]));
+        }
+      }
     }
+  }
+  if constexpr (APART) {
+#pragma unroll
+    for (int c = 0; c < COLS; ++c) acc[c] = add4(acc[c], low[c]);
   }
 }
 
-// out[db][c] (head dims 16 db .., column) += tile^T . w over the tile's rows
-// [row0, row0 + 32); w[c]: the lane's values of rows row0 + 4 g4 + i and row0 +
-// 16 + 4 g4 + i.  APART: the 32 rows are summed from zero and added by the vector
-// ALU, one rounding of the running sum instead of six.
-template <bool APART, int DH, int COLS>
-__device__ __forceinline__ void acc_rows(f32x4 (&out)[DH / 16][COLS], const char* tile, int row0, const Planes (&w)[COLS],
-                                         int col, int g4) {
+// tile^T . w over the tile's rows [row0, row0 + 32), to add(db, c, a, w[c]) for
+// every 16 head dims from 16 db and every column; w[c]: the lane's values of rows
+// row0 + 4 g4 + i and row0 + 16 + 4 g4 + i.
+template <int DH, int COLS, typename Add>
+__device__ __forceinline__ void acc_rows(const char* tile, int row0, const Planes (&w)[COLS], int col, int g4, Add add) {
   using T = Tile<DH>;
 #pragma unroll
   for (int db = 0; db < DH / 16; ++db) {
@@ -249,15 +273,7 @@ __device__ __forceinline__ void acc_rows(f32x4 (&out)[DH / 16][COLS], const char
       a.p[q] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
 #pragma unroll
-    for (int c = 0; c < COLS; ++c) {
-      if constexpr (APART) {
-        const f32x4 t = mma6(a, w[c], zero4());
-#pragma unroll
-        for (int r = 0; r < 4; ++r) out[db][c][r] += t[r];
-      } else {
-        out[db][c] = mma6(a, w[c], out[db][c]);
-      }
-    }
+    for (int c = 0; c < COLS; ++c) add(db, c, a, w[c]);
   }
 }
 
@@ -330,7 +346,7 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
         const int t0 = k0 + i * kAttnTile;
         f32x4 s[4][COLS];
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) dot_rows<DH, COLS>(s[kb], sK, kb * 16, qf, col, g4);
+        for (int kb = 0; kb < 4; ++kb) dot_rows<false, DH, COLS>(s[kb], sK, kb * 16, qf, col, g4);
         if (t0 + kAttnTile > k1) {
 #pragma unroll
           for (int kb = 0; kb < 4; ++kb)
@@ -378,7 +394,9 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
             }
             p[c] = split8<false>(t);
           }
-          acc_rows<true, DH, COLS>(oacc, sV, 32 * h, p, col, g4);
+          acc_rows<DH, COLS>(sV, 32 * h, p, col, g4, [&](int db, int c, const Planes& a, const Planes& w) {
+            oacc[db][c] = add4(oacc[db][c], mma_top(a, w, mma_low(a, w, zero4())));
+          });
         }
       });
 #pragma unroll
@@ -441,8 +459,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__
             for (int e = 0; e < 2; ++e) {
               const int row0 = 32 * h + 16 * e;
               f32x4 s[COLS], dp[COLS];
-              dot_rows<DH, COLS>(s, sK, row0, qf, col, g4);
-              dot_rows<DH, COLS>(dp, sV, row0, df, col, g4);
+              dot_rows<false, DH, COLS>(s, sK, row0, qf, col, g4);
+              dot_rows<true, DH, COLS>(dp, sV, row0, df, col, g4);
 #pragma unroll
               for (int c = 0; c < COLS; ++c)
 #pragma unroll
@@ -454,7 +472,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__
             Planes w[COLS];
 #pragma unroll
             for (int c = 0; c < COLS; ++c) w[c] = split8<false>(t[c]);
-            acc_rows<true, DH, COLS>(dq, sK, 32 * h, w, col, g4);
+            acc_rows<DH, COLS>(sK, 32 * h, w, col, g4, [&](int db, int c, const Planes& a, const Planes& x) {
+              dq[db][c] = add4(dq[db][c], add4(mma_top(a, x, zero4()), mma_low(a, x, zero4())));
+            });
           }
         };
         if (left >= kAttnTile) tile(std::false_type());
@@ -557,8 +577,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
             for (int e = 0; e < 2; ++e) {
               const int row0 = 32 * h + 16 * e;
               f32x4 s[COLS], dp[COLS];
-              dot_rows<DH, COLS>(s, sQ, row0, kf, col, g4);
-              dot_rows<DH, COLS>(dp, sD, row0, vf, col, g4);
+              dot_rows<true, DH, COLS>(s, sQ, row0, kf, col, g4);
+              dot_rows<true, DH, COLS>(dp, sD, row0, vf, col, g4);
               const float4 l4 = *reinterpret_cast<const float4*>(L + row0 + 4 * g4);
               const float4 d4 = *reinterpret_cast<const float4*>(Dd + row0 + 4 * g4);
               const float lr[4] = {l4.x, l4.y, l4.z, l4.w}, dr[4] = {d4.x, d4.y, d4.z, d4.w};
@@ -577,10 +597,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
             Planes w[COLS];
 #pragma unroll
             for (int c = 0; c < COLS; ++c) w[c] = split8<false>(p[c]);
-            acc_rows<false, DH, COLS>(dv, sD, 32 * h, w, col, g4);
+            acc_rows<DH, COLS>(sD, 32 * h, w, col, g4, [&](int db, int c, const Planes& a, const Planes& x) {
+              dv[db][c] = add4(mma_top(a, x, dv[db][c]), mma_low(a, x, zero4()));
+            });
 #pragma unroll
             for (int c = 0; c < COLS; ++c) w[c] = split8<false>(ds[c]);
-            acc_rows<false, DH, COLS>(dk, sQ, 32 * h, w, col, g4);
+            acc_rows<DH, COLS>(sQ, 32 * h, w, col, g4, [&](int db, int c, const Planes& a, const Planes& x) {
+              dk[db][c] = add4(mma_top(a, x, dk[db][c]), mma_low(a, x, zero4()));
+            });
           }
         };
         if (t0 + kAttnTile <= sg1 && (i < own || b.r0 >= sg0 - mem)) tile(std::false_type());

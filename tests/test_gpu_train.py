@@ -305,3 +305,16 @@ def test_products_round_both_ways_alike(dtype):
     got = {k: err[f"placer[1].{k}"] for k in ("b_o", "ln1_g", "ln1_b", "w_1", "b_1", "b_2", "ln2_g", "ln2_b")}
     _log("  opposed gradients", {k: f"{v:.1e}" for k, v in got.items()})
     assert max(got.values()) <= 2e-7, got
+
+
+@pytest.mark.parametrize("heads,seg", [(8, 128), (4, 128), (4, 96), (2, 128)])
+def test_attention_rounds_both_ways_alike(heads, seg):
+    """The gradients of W_q and W_k, differences of sums far larger than they are:
+    4e-7 to 9e-7 with fp32 instructions (each result rounded to either side), 3e-6
+    to 2e-5 where every row's dO . v, dQ and dK lean by 6e-9 of their size, as with
+    all plane pairs on one sum."""
+    err = _opposed("bf16" if heads == 4 else "f32", graph_sizes=(8193,), hidden=128, heads=heads, d_ff=256, seg_len=seg,
+                   mem_len=seg - 28)
+    got = {k: v for k, v in err.items() if k.startswith("placer") and k.split(".")[1] in ("w_q", "w_k", "w_v", "b_v")}
+    _log("  opposed gradients", {k: f"{v:.1e}" for k, v in got.items()})
+    assert max(got.values()) <= 1.5e-6, got
