@@ -46,6 +46,7 @@
 #include "device_common.h"
 #include "host_plan.h"
 #include "train_kernels.h"
+#include "train_planes.h"
 
 namespace gdp {
 namespace tr {
@@ -54,9 +55,6 @@ namespace {
 
 constexpr int kAttnTile = 64;    // rows staged per tile
 constexpr float kLog2e = 1.4426950408889634f;
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // The segment rows [r0, r1) of work block b (segments split into blocks of
 // `rows` rows; gt.blk the per-graph prefix of blocks).
@@ -75,38 +73,6 @@ __device__ __forceinline__ SegRows seg_rows(const GraphTable& gt, int b, int seg
   s.r0 = s.seg0 + (local % per) * rows;
   s.r1 = min(s.r0 + rows, s.seg1);
   return s;
-}
-
-// Eight fp32 values as three bf16 planes, v = p[0] + p[1] + p[2] exactly.
-struct Planes {
-  bf16x8 p[3];
-};
-// CLAMP: the median keeps an infinity's remainder, inf - inf, finite, so that an
-// infinite input stays infinite.
-template <bool CLAMP>
-__device__ __forceinline__ Planes split8(const float (&v)[8]) {
-  union P8 {
-    bf16x2 h[4];
-    bf16x8 q;
-  } p1, p2, p3;
-  constexpr float kBig = 2.6584559915698317e36f;   // 2^121
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x2 a = {v[2 * i], v[2 * i + 1]};
-    p1.h[i] = __builtin_convertvector(a, bf16x2);
-    f32x2 r = a - __builtin_convertvector(p1.h[i], f32x2);
-    if constexpr (CLAMP) {
-      r[0] = __builtin_amdgcn_fmed3f(r[0], -kBig, kBig);
-      r[1] = __builtin_amdgcn_fmed3f(r[1], -kBig, kBig);
-    }
-    p2.h[i] = __builtin_convertvector(r, bf16x2);
-    p3.h[i] = __builtin_convertvector(r - __builtin_convertvector(p2.h[i], f32x2), bf16x2);
-  }
-  Planes o;
-  o.p[0] = p1.q;
-  o.p[1] = p2.q;
-  o.p[2] = p3.q;
-  return o;
 }
 
 // 2^x by the hardware instruction (results below 2^-126 are 0).
@@ -170,7 +136,7 @@ struct Tile {
   __device__ __forceinline__ void store(char* s) const {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const Planes p = split8<true>(v[u]);
+      const Planes p = split8(v[u]);
       const int o = at(unit(u) / G, unit(u) % G);
 #pragma unroll
       for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(s + q * kPlane + o) = p.p[q];
@@ -202,7 +168,7 @@ struct RowOperand {
         if (ok) a = *reinterpret_cast<const float4*>(p + i);
         t[i] = a.x * mul; t[i + 1] = a.y * mul; t[i + 2] = a.z * mul; t[i + 3] = a.w * mul;
       }
-      k[s] = split8<true>(t);
+      k[s] = split8(t);
     }
     if constexpr (DH == 16) {      // B planes of the pairs (a3 b1 | a1 b3), (a2 b2 | a1 b2) and (a b1/2 | a b1/2)
       const Planes o = k[0];
@@ -311,6 +277,36 @@ __device__ __forceinline__ void for_tiles(char* lds, int tiles, Load load, Work 
   }
 }
 
+// Query q's attention over keys [k0, k1) one key at a time in fp32: m, the sum of
+// 2^(s - m) and the lane's rows 16 db + 4 g4 + r of the weighted values.
+template <int DH>
+__device__ __forceinline__ void attend_fp32(const float* __restrict__ qkv, int ld, int d, int q, int k0, int k1, int c0,
+                                            int g4, float mul, float& m, float& sum, f32x4 (&o)[DH / 16]) {
+  auto score = [&](int j) {
+    const float *x = qkv + (size_t)q * ld + c0, *y = qkv + (size_t)j * ld + d + c0;
+    float t = 0.f;
+    for (int i = 0; i < DH; ++i) t = fmaf(x[i] * mul, y[i], t);
+    return t;
+  };
+  m = -INFINITY;
+  sum = 0.f;
+#pragma unroll
+  for (int db = 0; db < DH / 16; ++db) o[db] = zero4();
+  for (int j = k0; j < k1; ++j) m = fmaxf(m, score(j));
+  for (int j = k0; j < k1 && sum == sum; ++j) {            // NaN stays NaN
+    const float p = exp2f(score(j) - m);
+    sum += p;
+#pragma unroll
+    for (int db = 0; db < DH / 16; ++db) {
+      const float4 v = *reinterpret_cast<const float4*>(qkv + (size_t)j * ld + 2 * d + c0 + db * 16 + 4 * g4);
+      o[db][0] = fmaf(p, v.x, o[db][0]);
+      o[db][1] = fmaf(p, v.y, o[db][1]);
+      o[db][2] = fmaf(p, v.z, o[db][2]);
+      o[db][3] = fmaf(p, v.w, o[db][3]);
+    }
+  }
+}
+
 template <int DH, int COLS>
 __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv, int d, int heads, int seg, int mem,
                                                   GraphTable gt, float scale, float* __restrict__ o,
@@ -392,7 +388,7 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
               t[r] = s[2 * h][c][r];
               t[4 + r] = s[2 * h + 1][c][r];
             }
-            p[c] = split8<false>(t);
+            p[c] = split8(t);
           }
           acc_rows<DH, COLS>(sV, 32 * h, p, col, g4, [&](int db, int c, const Planes& a, const Planes& w) {
             oacc[db][c] = add4(oacc[db][c], mma_top(a, w, mma_low(a, w, zero4())));
@@ -404,6 +400,18 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
     lsum[c] += xor_shfl(lsum[c], 16);
     lsum[c] += xor_shfl(lsum[c], 32);
     if (q[c] >= b.r1) continue;
+    // a key or value that is infinite, or rounds to a bf16 infinity, has no planes
+    float any = lsum[c] * 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) any = fmaf(oacc[db][c][r], 0.f, any);
+    if (any != any) {
+      f32x4 t[DB];
+      attend_fp32<DH>(qkv, ld, d, q[c], k0, k1, c0, g4, scale * kLog2e, m[c], lsum[c], t);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) oacc[db][c] = t[db];
+    }
     const float inv = 1.0f / lsum[c];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -471,7 +479,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__
             }
             Planes w[COLS];
 #pragma unroll
-            for (int c = 0; c < COLS; ++c) w[c] = split8<false>(t[c]);
+            for (int c = 0; c < COLS; ++c) w[c] = split8(t[c]);
             acc_rows<DH, COLS>(sK, 32 * h, w, col, g4, [&](int db, int c, const Planes& a, const Planes& x) {
               dq[db][c] = add4(dq[db][c], add4(mma_top(a, x, zero4()), mma_low(a, x, zero4())));
             });
@@ -596,12 +604,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
             }
             Planes w[COLS];
 #pragma unroll
-            for (int c = 0; c < COLS; ++c) w[c] = split8<false>(p[c]);
+            for (int c = 0; c < COLS; ++c) w[c] = split8(p[c]);
             acc_rows<DH, COLS>(sD, 32 * h, w, col, g4, [&](int db, int c, const Planes& a, const Planes& x) {
               dv[db][c] = add4(mma_top(a, x, dv[db][c]), mma_low(a, x, zero4()));
             });
 #pragma unroll
-            for (int c = 0; c < COLS; ++c) w[c] = split8<false>(ds[c]);
+            for (int c = 0; c < COLS; ++c) w[c] = split8(ds[c]);
             acc_rows<DH, COLS>(sQ, 32 * h, w, col, g4, [&](int db, int c, const Planes& a, const Planes& x) {
               dk[db][c] = add4(mma_top(a, x, dk[db][c]), mma_low(a, x, zero4()));
             });

@@ -44,6 +44,7 @@
 #include "device_common.h"
 #include "lds_dma.h"
 #include "train_kernels.h"
+#include "train_planes.h"
 
 namespace gdp {
 namespace tr {
@@ -63,42 +64,10 @@ __device__ __forceinline__ int tile_at(int row, int g) {
   else return row * 32 + ((g ^ (((row >> 2) ^ (row >> 3)) & 1)) << 4);
 }
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// Eight fp32 values as three bf16 planes, v = p[0] + p[1] + p[2] exactly.
-struct Split8 {
-  bf16x8 p[3];
-};
-__device__ __forceinline__ Split8 split8(const float (&v)[8]) {
-  union P8 {
-    bf16x2 h[4];
-    bf16x8 q;
-  } p1, p2, p3;
-  // An infinity's remainder is inf - inf: the median turns it into a finite
-  // value beyond any real remainder (at most 2^119), so infinity stays infinity.
-  constexpr float kBig = 2.6584559915698317e36f;   // 2^121
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x2 a = {v[2 * i], v[2 * i + 1]};
-    p1.h[i] = __builtin_convertvector(a, bf16x2);
-    f32x2 r = a - __builtin_convertvector(p1.h[i], f32x2);
-    r[0] = __builtin_amdgcn_fmed3f(r[0], -kBig, kBig);
-    r[1] = __builtin_amdgcn_fmed3f(r[1], -kBig, kBig);
-    p2.h[i] = __builtin_convertvector(r, bf16x2);
-    p3.h[i] = __builtin_convertvector(r - __builtin_convertvector(p2.h[i], f32x2), bf16x2);
-  }
-  Split8 o;
-  o.p[0] = p1.q;
-  o.p[1] = p2.q;
-  o.p[2] = p3.q;
-  return o;
-}
-
 // Eight values as 1 or 3 bf16 planes of 16 bytes at byte offset `at`, planes
 // `plane` bytes apart.
 __device__ __forceinline__ void store_planes(char* s, int at, int plane, const float (&v)[8]) {
-  const Split8 o = split8(v);
+  const Planes o = split8(v);
 #pragma unroll
   for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(s + q * plane + at) = o.p[q];
 }
@@ -239,6 +208,62 @@ __device__ __forceinline__ void epilogue(const GemmStrided<TA, TB>& g, int m, in
 
 }  // namespace
 
+// sum over [k0, k1) of A(m, k) B(k, n), one product at a time in fp32.
+template <typename TA, typename TB>
+__device__ __forceinline__ float dot_fp32(const GemmStrided<TA, TB>& g, int m, int n, int k0, int k1) {
+  const TA* a = g.a + (size_t)m * g.sam;
+  const TB* b = g.b + (size_t)n * g.sbn;
+  float t = 0.f;
+  for (int k = k0; k < k1 && t == t; k += 8) {             // NaN stays NaN
+    float x[8], y[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const size_t q = (size_t)min(k + i, k1 - 1);
+      x[i] = (float)a[q * g.sak];
+      y[i] = (float)b[q * g.sbk];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (k + i < k1) t = fmaf(x[i], y[i], t);
+  }
+  return t;
+}
+// The results of a lane's R x C blocks of E that are not finite, formed again by
+// dot(i, j, e): where an operand is infinite or rounds to a bf16 infinity (from
+// 3.396e38), its planes and those of what it meets give inf - inf or inf * 0.
+template <int R, int C, int E, typename Acc, typename Dot>
+__device__ __forceinline__ void form_again(Acc (&acc)[R][C], Dot dot) {
+  static_assert(R * C * E <= 64, "one bit a result");
+  float any = 0.f;                                         // NaN if one is not finite
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+      for (int e = 0; e < E; ++e) any = fmaf(acc[i][j][e], 0.f, any);
+  if (any == any) return;
+  uint64_t todo = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (!isfinite(acc[i][j][e])) todo |= 1ull << ((i * C + j) * E + e);
+  while (todo) {
+    const int at = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    const float t = dot(at / E / C, at / E % C, at % E);
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (at == (i * C + j) * E + e) acc[i][j][e] = t;
+  }
+}
+
 // VEC: vector loads and float4 stores are aligned (host-checked).
 template <typename TA, typename TB, int BM, bool AKF, bool BKF, bool VEC, int EPI>
 __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, int k_per_split, float* partial, int nt,
@@ -359,6 +384,16 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
   constexpr int NQ = MT * MT / 256;
   auto row_of = [&](int i) { return m0 + mw + MT * i + col; };
   auto col_of = [&](int j, int q) { return n0 + nw + MT * j + (MT == 16 ? 4 * gr : 8 * q + 4 * gr); };
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < MT * MT / 64; ++r) acc[i][j][r] += low[i][j][r];
+  if constexpr (PA * PB > 1)
+    form_again<NB, NB, MT * MT / 64>(acc, [&](int i, int j, int r) {
+      return dot_fp32(g, min(row_of(i), g.M - 1), min(col_of(j, r / 4) + r % 4, g.N - 1), kb, ke);
+    });
   EpiIn<EPI, 4> in[VEC ? NB : 1][VEC ? NB : 1][VEC ? NQ : 1];
   if constexpr (VEC && EPI != E_RAW) {
 #pragma unroll
@@ -377,8 +412,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
         const int m = row_of(i), n = col_of(j, q);
         if (m >= g.M || n >= g.N) continue;
         float v[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] += low[i][j][4 * q + r];
         float* o = partial + ((size_t)z * g.M + m) * g.N + n;
         if constexpr (VEC) {
           if (partial) *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
@@ -452,7 +485,7 @@ __global__ __launch_bounds__(256, 2) void k_linear_split(GemmStrided<float, bf16
     // rows (4 + 2 + 4 loads)
     dma::wait_vm_barrier<10>();
     fetch(s + 2);
-    Split8 fa[2];
+    Planes fa[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) fa[i] = split8(raw[set][i]);
     load(set, s + 2);
@@ -475,6 +508,15 @@ __global__ __launch_bounds__(256, 2) void k_linear_split(GemmStrided<float, bf16
   }
   dma::wait_loads_then_barrier();                        // no direct load outlives the work-group
   auto row_of = [&](int i) { return m0 + wave * 32 + i * 16 + col; };
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] += low[i][j][r];
+  form_again<2, 8, 4>(acc, [&](int i, int j, int r) {
+    return dot_fp32(g, min(row_of(i), g.M - 1), n0 + 16 * j + 4 * g4 + r, 0, g.K);
+  });
   EpiIn<EPI, 4> in[2][8];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -488,7 +530,7 @@ __global__ __launch_bounds__(256, 2) void k_linear_split(GemmStrided<float, bf16
       if (m >= g.M) continue;
       float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = acc[i][j][r] + low[i][j][r];
+      for (int r = 0; r < 4; ++r) v[r] = acc[i][j][r];
       epilogue<EPI, 4>(g, m, n, in[i][j], v);
     }
 }

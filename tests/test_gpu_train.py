@@ -318,3 +318,86 @@ def test_attention_rounds_both_ways_alike(heads, seg):
     got = {k: v for k, v in err.items() if k.startswith("placer") and k.split(".")[1] in ("w_q", "w_k", "w_v", "b_v")}
     _log("  opposed gradients", {k: f"{v:.1e}" for k, v in got.items()})
     assert max(got.values()) <= 1.5e-6, got
+
+
+def _extreme(case, dtype, n, hidden):
+    """A policy and a graph whose products meet operands that a bf16 cannot hold,
+    every result of the forward finite."""
+    cfg = W.get_config("tiny_layered_256").replace(dtype=dtype, graph_sizes=(n,), hidden=hidden, heads=hidden // 32,
+                                                   placer_layers=1, film=False)
+    g, w = W.make_graph(cfg), W.make_weights(cfg)
+    x = g.x.copy()
+    rows = [0, n // 2, n - 1]
+
+    def put(layer, name, change):
+        a = layer[name][0].copy()
+        change(a)
+        layer[name] = W._finish(cfg, a)
+
+    def negative(*cols):
+        def change(a):
+            a[:, cols] = -0.01
+        return change
+    if case in ("huge", "infinite"):           # features in column 3
+        x[rows, 3] = 3.4e38 if case == "huge" else np.inf
+        put(w.gnn[0], "w_self", negative(3))   # the rows' ReLU is 0, their sigmoids 0 or 1
+        if case == "huge":
+            put(w.gnn[0], "w_pool", negative(3))
+    elif case == "huge_hidden":                # layer 0's output 3.399e38 in column 5, from features bf16 can hold
+        x[rows, 3], x[rows, 4] = 2.0 ** 127, 1.5 * 2.0 ** 119
+        put(w.gnn[0], "w_pool", negative(3, 4))
+
+        def one_large(a):
+            a[:, [3, 4]] = -0.01
+            a[5, [3, 4]] = 255 / 128, 1.0
+        put(w.gnn[0], "w_self", one_large)
+        put(w.gnn[1], "w_self", negative(5))
+        put(w.gnn[1], "w_pool", negative(5))
+    else:                                      # keys of minus infinity for part of the rows: no weight
+        def keys(a):
+            a[0] = 0.0                         # query column 0: -1, from its bias
+            a[hidden] = 0.0
+            a[hidden, :2] = 3e38
+        put(w.placer[0], "w_qkv", keys)
+
+        def query(a):
+            a[0] = -1.0
+        put(w.placer[0], "b_qkv", query)
+    return cfg, W.graph_from_arrays(cfg, [0, n], g.row_ptr, g.col_idx, x), w
+
+
+@pytest.mark.parametrize("case,dtype,n,hidden", [
+    ("huge", "f32", 300, 64), ("huge", "f32", 32800, 256), ("huge_hidden", "f32", 300, 128),
+    ("huge_hidden", "bf16", 300, 64), ("huge_hidden", "bf16", 32800, 256), ("infinite", "f32", 300, 64),
+    ("infinite", "f32", 32800, 256), ("infinite_keys", "f32", 300, 64), ("infinite_keys", "bf16", 300, 128)])
+def test_operands_beyond_bf16(case, dtype, n, hidden):
+    """Infinite operands and finite ones that round to a bf16 infinity (3.396e38 to
+    3.403e38), in 64 x 64 and 128 x 128 tiles and in the bf16 weights' kernel: what
+    fp32 products give, an infinity only where one of them is."""
+    import torch
+    cfg, g, w = _extreme(case, dtype, n, hidden)
+    _log("operands beyond bf16", case, dtype, n)
+    t = _trainer(cfg, g, w)
+    logits, _ = t.forward()
+    dl = (np.random.default_rng(9).normal(size=(n, cfg.n_devices)) / np.sqrt(n)).astype(np.float32)
+    t.backward(torch.from_numpy(dl).cuda())
+    torch.cuda.synchronize()
+    gnn, pl, hd = w.f64()
+    x = np.where(np.isinf(g.x), 1e30, g.x)     # in the oracle as good as infinite (its masks are products)
+    ref = PG.policy_backward(g.graph_ptr, g.row_ptr, g.col_idx, x, gnn, pl, hd["w_out"], hd["b_out"],
+                             dl.astype(np.float64), fanout=cfg.fanout, nb_seed=cfg.nb_seed, n_heads=cfg.heads,
+                             seg_len=cfg.seg_len, mem_len=cfg.mem_len, film=False, decisions=t.decisions())
+    # the oracle's own decisions: the GPU's ReLU turns a NaN into 0, which pinned ones would follow
+    own = O.policy_forward(g.graph_ptr, g.row_ptr, g.col_idx, x, gnn, pl, hd["w_out"], hd["b_out"], fanout=cfg.fanout,
+                           nb_seed=cfg.nb_seed, n_heads=cfg.heads, seg_len=cfg.seg_len, mem_len=cfg.mem_len,
+                           k_samples=1, sample_seed=0, film=False)["logits"]
+    assert np.isfinite(own).all()
+    assert rel_err_rows(to_np(logits), own) <= TOL[dtype]
+    if case == "infinite_keys":
+        return                                 # a gradient through them is 0 * infinity
+    if case == "infinite":                     # and so is that of the infinite features' weights
+        for k in ("w_self", "w_pool"):
+            assert np.isnan(to_np(t.grad_gnn[0][k][:, 3])).all()
+            ref["gnn"][0][k][:, 3] = 0.0
+            t.grad_gnn[0][k][:, 3] = 0.0
+    _compare_grads(t, ref, cfg, film=False)
