@@ -276,6 +276,8 @@ int check_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p) {
   return GDP_OK;
 }
 
+bool vec_stride(long stride) { return stride >= 0 && stride < (1L << 23); }
+
 void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* pl, TrainPlan* t) {
   const size_t N = (size_t)g->n_nodes, E = (size_t)g->n_edges, H = (size_t)gnn->hidden, d = (size_t)pl->d_model;
   const size_t G = (size_t)g->n_graphs, dff = (size_t)pl->d_ff, F = (size_t)g->feat_dim;

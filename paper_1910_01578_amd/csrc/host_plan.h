@@ -98,6 +98,11 @@ struct TrainPlan {
 };
 int check_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p);
 void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, TrainPlan* t);
+// Whether the update step's products may use vector loads on an operand whose rows
+// are `stride` elements apart: those index up to kVecRows rows from a tile's first
+// by a signed 24-bit product, exact below 2^23.  feat_dim and d_ff have no bound.
+constexpr int kVecRows = 128;
+bool vec_stride(long stride);
 void plan_embed(const gdp_graph* g, const gdp_gnn* gnn, EmbedPlan* p);
 void plan_place(const gdp_graph* g, const gdp_placer* pl, PlacePlan* p);
 void plan_sample(const gdp_graph* g, int32_t k_samples, SamplePlan* p);

@@ -42,6 +42,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "host_plan.h"
 #include "lds_dma.h"
 #include "train_kernels.h"
 #include "train_planes.h"
@@ -274,6 +275,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
   constexpr int kPlane = BM * KS * 2, kBuf = (PA + PB) * kPlane;
   typedef float acc_t __attribute__((ext_vector_type(MT * MT / 64)));
   __shared__ __attribute__((aligned(16))) char lds[2 * kBuf];
+  static_assert(BM <= kVecRows && KS <= kVecRows, "rows indexed by a 24-bit product");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane % MT, gr = lane / MT;
   const int mw = (wave >> 1) * WT, nw = (wave & 1) * WT;
   // consecutive tiles of a row block share its rows of A: keep them on one XCD
@@ -632,6 +634,7 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
   bool vec = g.N % 4 == 0 && g.N >= 4 && g.M >= 2 && g.K >= 1;
   vec = vec && (akf ? g.K % 32 == 0 && vec_aligned(g.a, g.sam, 16) : vec_aligned(g.a, g.sak, 2 * sizeof(TA)));
   vec = vec && (bkf ? g.K % 32 == 0 && vec_aligned(g.b, g.sbn, 16) : vec_aligned(g.b, g.sbk, 2 * sizeof(TB)));
+  vec = vec && vec_stride(akf ? g.sam : g.sak) && vec_stride(bkf ? g.sbn : g.sbk);
   vec = vec && (!partial || vec_aligned(partial, 0, 16));
   vec = vec && (vec_aligned(g.c, g.ldc, 16) && (!g.mask || vec_aligned(g.mask, g.ldm, 16)) &&
                 (!g.res || vec_aligned(g.res, g.ldr, 16)));

@@ -498,6 +498,34 @@ static void train_paths() {
   }
 }
 
+// The offset that a lane's vector load forms, row * stride, by a signed 24-bit
+// multiplication into 32 bits, wherever vec_stride() allows vector loads.
+static uint32_t mul24(int32_t a, int32_t b) {
+  auto low = [](int32_t v) { return (int32_t)((uint32_t)v << 8) >> 8; };
+  return (uint32_t)((int64_t)low(a) * low(b));
+}
+static void vec_stride_paths() {
+  const long strides[] = {0,         1,         64,        768,       1 << 20,  (1 << 22) + 128, (1 << 23) - 128, (1 << 23) - 1, 1 << 23,
+                          (1 << 23) + 32, 1 << 24, (1 << 25) + 128, 1L << 30, INT32_MAX, -1};
+  int allowed = 0;
+  for (long s : strides) {
+    ++g_checks;
+    if (!vec_stride(s)) continue;
+    ++allowed;
+    for (int row = 0; row < kVecRows; ++row)
+      if ((int64_t)mul24(row, (int32_t)s) != row * s) {
+        ++g_failures;
+        printf("FAIL row %d of stride %ld: offset %u\n", row, s, mul24(row, (int32_t)s));
+        break;
+      }
+  }
+  ++g_checks;
+  if (allowed != 8) {
+    ++g_failures;
+    printf("FAIL vec_stride allows %d of the strides\n", allowed);
+  }
+}
+
 static void error_text() {
   clear_error();
   ++g_checks;
@@ -522,6 +550,7 @@ int main() {
   split_paths();
   blocks_below_paths();
   train_paths();
+  vec_stride_paths();
   error_text();
   printf("%d checks, %d failures\n", g_checks, g_failures);
   return g_failures == 0 ? 0 : 1;
