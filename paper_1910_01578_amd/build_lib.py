@@ -28,7 +28,7 @@ DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-p
 FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-pass-failed"],
               "train_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
-SOURCES = ["graph_kernels.hip", "gemm.hip", "layer.hip", "attention.hip", "placer_kernels.hip", "sample.hip", "ppo.hip", "evaluate.hip", "train.hip", "train_gemm.hip", "train_attn.hip",
+SOURCES = ["graph_kernels.hip", "gemm.hip", "layer.hip", "attention.hip", "placer_kernels.hip", "sample.hip", "ppo.hip", "evaluate.hip", "evaluate_lanes.hip", "train.hip", "train_gemm.hip", "train_attn.hip",
            "gdp_api.hip", "host_plan.cpp"]
 
 

@@ -576,8 +576,8 @@ int eval_ring(const int32_t* graph_ptr, int G, int K) {
 }
 
 hipError_t launch_evaluate(const EvalLaunch& L, hipStream_t s) {
-  hipLaunchKernelGGL(k_window_lists, dim3(L.windows), dim3(256), 0, s, L.in_ptr, L.in_idx, L.op_cost, L.out_xfer,
-                     *L.window_table, reinterpret_cast<int4*>(L.hdr), reinterpret_cast<int4*>(L.win),
+  hipLaunchKernelGGL(k_window_lists, dim3(L.blocks), dim3(256), 0, s, L.in_ptr, L.in_idx, L.op_cost, L.out_xfer,
+                     *L.table, reinterpret_cast<int4*>(L.hdr), reinterpret_cast<int4*>(L.win),
                      reinterpret_cast<int2*>(L.rec));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -598,7 +598,7 @@ hipError_t launch_evaluate(const EvalLaunch& L, hipStream_t s) {
   a.makespan = L.makespan;
   a.valid = L.valid;
   a.run_time = L.run_time;
-  const GraphTable& wt = *L.window_table;
+  const GraphTable& wt = *L.table;
   CapTable caps;
   for (int i = 0; i < GDP_MAX_GRAPHS; ++i) caps.cap[i] = i < wt.n ? L.mem_cap[i] : 0;
   const dim3 grid((unsigned)wt.n * (unsigned)L.K), block(256);

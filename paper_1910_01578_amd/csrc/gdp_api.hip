@@ -18,7 +18,7 @@ namespace gdp {
 static_assert(kPoolRows == kMeanpoolRows, "mean-pool chunk size");
 static_assert(kAttnQ == kAttnBlockQ, "attention query block");
 static_assert(kSampleRows == kSampleChunk, "sampling chunk");
-static_assert(kEvalWindowRows == kEvalWindow, "evaluator window");
+static_assert(kEvalWindowRows == kEvalWindow && kEvalChunkRows == kEvalChunk, "evaluator blocks");
 
 // ---------------------------------------------------------------------------
 // Event timer (diagnostics): an event pair around every launch of a selected
@@ -829,8 +829,7 @@ extern "C" int gdp_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_sam
                                                  at<int>(ws, pl.scan_tmp), st));
   GDP_LAUNCH(GDP_K_EVALUATE, launch_fill_reverse(g->row_ptr, g->col_idx, in_ptr, N, g->n_edges, counters + N, in_idx,
                                                  st));
-  GraphTable wt = make_table(g);
-  const int windows = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalWindowRows, wt.blk);
+  GraphTable table = make_table(g);
   EvalLaunch L;
   L.placements = placements;
   L.op_cost = op_cost;
@@ -840,8 +839,8 @@ extern "C" int gdp_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_sam
   L.in_ptr = in_ptr;
   L.in_idx = in_idx;
   L.n_edges = g->n_edges;
-  L.window_table = &wt;
-  L.windows = windows;
+  L.table = &table;
+  L.blocks = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, pl.by_lanes ? kEvalChunkRows : kEvalWindowRows, table.blk);
   L.n = N;
   L.D = n_devices;
   L.K = k_samples;
@@ -851,10 +850,11 @@ extern "C" int gdp_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_sam
   L.rec = at<void>(ws, pl.rec);
   L.far = at<unsigned>(ws, pl.far);
   L.far_stride = pl.far_stride;
+  L.memsum = at<void>(ws, pl.memsum);
   L.makespan = makespan;
   L.valid = valid;
   L.run_time = run_time;
-  GDP_LAUNCH(GDP_K_EVALUATE, launch_evaluate(L, st));
+  GDP_LAUNCH(GDP_K_EVALUATE, pl.by_lanes ? launch_evaluate_lanes(L, st) : launch_evaluate(L, st));
   return GDP_OK;
 }
 

@@ -239,16 +239,25 @@ void plan_place(const gdp_graph* g, const gdp_placer* pl, PlacePlan* p) {
   p->qkv2 = p->split > 0 ? carve_add(&p->c, N * 3 * d * es) : p->qkv;
 }
 
-void plan_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k, EvalPlan* p) {
-  (void)n_devices;
-  const size_t N = (size_t)g->n_nodes, E = (size_t)g->n_edges;
-  int32_t blk[GDP_MAX_GRAPHS + 1];
-  p->windows = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalWindowRows, blk);
+static int longest_graph(const gdp_graph* g) {
   int longest = 0;
   for (int i = 0; i < g->n_graphs; ++i) {
     const int n = g->graph_ptr_h[i + 1] - g->graph_ptr_h[i];
     if (n > longest) longest = n;
   }
+  return longest;
+}
+
+bool eval_by_lanes(const gdp_graph* g, int32_t k_samples) {
+  const int64_t waves = (int64_t)g->n_graphs * ((k_samples + 63) / 64);
+  return waves >= 256 && longest_graph(g) <= (waves < 2048 ? waves : 2048) && g->n_edges <= 3 * (int64_t)g->n_nodes;
+}
+
+void plan_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k, EvalPlan* p) {
+  const size_t N = (size_t)g->n_nodes, E = (size_t)g->n_edges;
+  int32_t blk[GDP_MAX_GRAPHS + 1];
+  const int windows = prefix_blocks_rows(g->graph_ptr_h, g->n_graphs, kEvalWindowRows, blk);
+  p->by_lanes = eval_by_lanes(g, k);
   p->far_stride = (N + 63) / 64 * 64;
   carve_init(&p->c);
   p->counters = carve_add(&p->c, (2 * N + 1) * 4);
@@ -256,10 +265,12 @@ void plan_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k, EvalPlan* p
   p->in_ptr = carve_add(&p->c, (N + 1) * 4);
   p->s_ptr = carve_add(&p->c, (N + 1) * 4);
   p->in_idx = carve_add(&p->c, (E > 0 ? E : 1) * 4);
-  p->hdr = carve_add(&p->c, N * 16);
-  p->win = carve_add(&p->c, (size_t)p->windows * 16);
   p->rec = carve_add(&p->c, (E > 0 ? E : 1) * 8);
-  p->far = carve_add(&p->c, longest > kEvalMinRing ? (size_t)k * p->far_stride * 4 : 0);
+  p->hdr = carve_add(&p->c, p->by_lanes ? 0 : N * 16);
+  p->win = carve_add(&p->c, p->by_lanes ? 0 : (size_t)windows * 16);
+  p->memsum = carve_add(&p->c, p->by_lanes ? (size_t)g->n_graphs * (size_t)k * (size_t)n_devices * 8 : 0);
+  if (p->by_lanes) p->far = carve_add(&p->c, ((size_t)k + 63) / 64 * 64 * N * 4);
+  else p->far = carve_add(&p->c, longest_graph(g) > kEvalMinRing ? (size_t)k * p->far_stride * 4 : 0);
 }
 
 int check_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p) {

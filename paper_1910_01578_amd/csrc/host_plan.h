@@ -71,10 +71,20 @@ struct SamplePlan {
 struct EvalPlan {
   Carve c;
   size_t counters;    // [in_deg: N | cursor: N | spare: 1]
-  size_t scan_tmp, in_ptr, s_ptr, in_idx, hdr, win, rec, far;
+  size_t scan_tmp, in_ptr, s_ptr, in_idx, hdr, win, rec, far, memsum;
   size_t far_stride;  // words per sample of the finish times kept in memory
-  int windows;
+  bool by_lanes;      // one lane a sample
 };
+// Whether one lane a sample (a wave per graph and 64 samples, 0.6 us an op) is
+// faster than a work-group a sample (1.1 ns a window of 64 ops and 1.9 ns a graph,
+// the chip full).  The latter is ahead until the waves fill the chip, the longer
+// the graphs the later.  Graphs of 15 - 30, 65 - 130, 300 - 600 and 600 - 1,200 ops,
+// by lanes / by work-groups, us: 128 waves 68 / 65, 94 / 75, 339 / 129, 382 / 191;
+// 512 waves 90 / 137, 127 / 181, 384 / 372, 603 / 584; 2,048 waves 221 / 396,
+// 340 / 587, 1,123 / 1,320, 1,945 / 2,310; 2,000 ops, 2,048 waves 3,350 / 3,600.
+// Lanes take 0.2 us more per edge (8 predecessors an op: 20 times the work-group's
+// time), hence the limit on those.
+bool eval_by_lanes(const gdp_graph* g, int32_t k_samples);
 void plan_evaluate(const gdp_graph* g, int32_t n_devices, int32_t k_samples, EvalPlan* p);
 
 // The update step: what the training forward keeps (store) and the backward's
@@ -115,6 +125,7 @@ constexpr int kSplitRows = 256 * 128;
 constexpr int kSampleRows = 256;    // nodes per sampling work-group
 constexpr int kColSumRows = 64;     // rows per column-sum chunk of the backward pass
 constexpr int kEvalWindowRows = 64;  // nodes per window of the evaluator
+constexpr int kEvalChunkRows = 256;  // nodes per device-memory work-group of the evaluator by lanes
 constexpr int kEvalMinRing = 4096;   // graphs up to this length never need their finish times in memory
 
 }  // namespace gdp

@@ -237,22 +237,25 @@ struct EvalLaunch {
   const int* in_ptr;           // [n + 1]
   const int* in_idx;           // [n_edges]
   int64_t n_edges;
-  const GraphTable* window_table;  // graphs and their kEvalWindow-node windows (blk)
-  int windows;
+  const GraphTable* table;     // graphs and their blocks (blk): kEvalWindow nodes, by lanes kEvalChunk
+  int blocks;
   int n, D, K;
   double time_unit;
   void* hdr;                   // scratch: n int4
-  void* win;                   // scratch: windows int4
+  void* win;                   // scratch: blocks int4
   void* rec;                   // scratch: n_edges int2
-  unsigned* far;               // scratch: K * far_stride uint32 when a graph is longer than eval_ring()
+  unsigned* far;               // scratch: K * far_stride uint32 when a graph is longer than eval_ring(),
+                               // by lanes ceil(K / 64) * 64 * n
   size_t far_stride;           // >= n, a multiple of 64
+  void* memsum;                // scratch, by lanes: G * K * D uint64
   int64_t* makespan;           // [G, K]
   unsigned char* valid;        // [G, K]
   float* run_time;             // [G, K] or null
 };
-constexpr int kEvalWindow = 64;
+constexpr int kEvalWindow = 64, kEvalChunk = 256;
 // Nodes whose finish times stay on chip for G graphs and K samples.
 int eval_ring(const int32_t* graph_ptr, int G, int K);
 hipError_t launch_evaluate(const EvalLaunch& L, hipStream_t s);
+hipError_t launch_evaluate_lanes(const EvalLaunch& L, hipStream_t s);
 
 }  // namespace gdp

@@ -526,6 +526,53 @@ static void vec_stride_paths() {
   }
 }
 
+// gdp_evaluate's choice between a lane and a work-group a sample, and that a
+// workspace for K samples serves every smaller K on either side of it.
+static void eval_route_paths() {
+  auto graph = [](int graphs, int nodes, int64_t edges, std::vector<int32_t>* ptr) {
+    ptr->clear();
+    for (int i = 0; i <= graphs; ++i) ptr->push_back(i * nodes);
+    gdp_graph g;
+    memset(&g, 0, sizeof(g));
+    g.n_graphs = graphs;
+    g.graph_ptr_h = ptr->data();
+    g.n_nodes = graphs * nodes;
+    g.n_edges = edges * g.n_nodes;
+    g.row_ptr = g.col_idx = (const int32_t*)fake(0x100000);
+    g.x = fake(0x100000);
+    g.feat_dim = 32;
+    return g;
+  };
+  struct {
+    int graphs, nodes, edges, k;
+    bool lanes;
+  } cases[] = {{1, 52000, 2, 64, false},  {1, 2500, 2, 16, false},  {128, 30, 1, 64, false},   {128, 30, 1, 128, true},
+               {128, 256, 1, 128, true},  {128, 257, 1, 128, false}, {128, 600, 2, 256, false}, {128, 500, 2, 256, true},
+               {128, 1200, 2, 1024, true}, {128, 2100, 2, 1024, false}, {128, 30, 8, 1024, false}, {1, 100, 1, 16384, true},
+               {1, 300, 1, 16384, false}, {8, 30, 1, 4096, true}};
+  for (const auto& c : cases) {
+    std::vector<int32_t> ptr;
+    const gdp_graph g = graph(c.graphs, c.nodes, c.edges, &ptr);
+    ++g_checks;
+    if (eval_by_lanes(&g, c.k) != c.lanes) {
+      ++g_failures;
+      printf("FAIL eval_by_lanes %d x %d, %d samples\n", c.graphs, c.nodes, c.k);
+    }
+    size_t before = 0;
+    for (int k = 1; k <= 4 * c.k && k <= 65535; k += k < 1000 ? 1 : 97) {
+      EvalPlan p;
+      plan_evaluate(&g, 4, k, &p);
+      ++g_checks;
+      if (p.c.total < before) {
+        ++g_failures;
+        printf("FAIL evaluator workspace shrinks at %d samples (%d x %d)\n", k, c.graphs, c.nodes);
+        break;
+      }
+      before = p.c.total;
+    }
+  }
+}
+
 static void error_text() {
   clear_error();
   ++g_checks;
@@ -551,6 +598,7 @@ int main() {
   blocks_below_paths();
   train_paths();
   vec_stride_paths();
+  eval_route_paths();
   error_text();
   printf("%d checks, %d failures\n", g_checks, g_failures);
   return g_failures == 0 ? 0 : 1;

@@ -186,3 +186,41 @@ def test_evaluate_windows_and_rings(n, K, D, dense, far, far_span):
     pl = np.where(rng.random((K, n)) < skew, rng.integers(0, D, (K, 1)), rng.integers(0, D, (K, n))).astype(np.int32)
     _check(g, costs, pl, D, gdp.Evaluator(gdp.DeviceGraph(g, base.dtype), D, K, costs))
     _log("evaluate windows", n, K, "ok")
+
+
+@pytest.mark.parametrize("sizes,K,D", [
+    ((256,) + (1, 2, 63, 64, 65, 129, 255) * 18 + (3,), 128, 8),   # 256 waves, up to 256 ops
+    ((90, 130), 8200, 64),                                         # the last block of samples 8 of 64
+    ((500, 300) * 8, 2100, 3),                                     # past the ring of 256 nodes
+])
+def test_evaluate_a_lane_a_sample(sizes, K, D):
+    """Many short graphs and samples, one lane a sample: ragged sizes and blocks of
+    samples, predecessors behind the ring, one graph past the time range."""
+    import torch
+
+    from paper_1910_01578_amd import gdp
+    c = W.get_config("tiny_layered_256").replace(graph_sizes=sizes)
+    parts = [_dag(n, np.random.default_rng(n), 0, n // 4, n // 2) if n > 8 else _dag(n, None, 0, 0, 0) for n in sizes]
+    starts = np.concatenate([[0], np.cumsum(sizes)])
+    edges = np.concatenate([[0], np.cumsum([p[1].size for p in parts])])
+    row_ptr = np.concatenate([[0]] + [p[0][1:] + e for p, e in zip(parts, edges)])
+    col = np.concatenate([p[1] + s for p, s in zip(parts, starts)])
+    rng = np.random.default_rng(K)
+    n = int(starts[-1])
+    g = W.graph_from_arrays(c, starts, row_ptr, col, W.make_features(c, n, rng))
+    cost = rng.integers(0, 50, n).astype(np.int32)
+    cost[0] = 2 ** 26
+    cap = np.array([100 * s // D for s in sizes], np.int64)
+    costs = W.OpCosts(cost, rng.integers(0, 90, n).astype(np.int32), rng.integers(1, 200, n).astype(np.int32), cap)
+    pl = rng.integers(0, D, (K, n)).astype(np.int32)
+    ev = gdp.Evaluator(gdp.DeviceGraph(g, c.dtype), D, K, costs)
+    mk, valid, _ = ev.evaluate(torch.from_numpy(pl).cuda())
+    torch.cuda.synchronize()
+    keep = np.concatenate([np.arange(min(K, 130)), np.arange(max(0, K - 130), K)]) if K > 260 else np.arange(K)
+    ref = O.simulate_placements(g.graph_ptr, g.row_ptr, g.col_idx, pl[keep], D, costs.op_cost, costs.out_xfer,
+                                costs.op_mem, costs.mem_cap)
+    got = mk.cpu().numpy()[:, keep]
+    assert np.all(got[0] == -1) and ref["makespan"][0].min() >= 2 ** 26
+    assert np.array_equal(got[1:], ref["makespan"][1:])
+    assert np.array_equal(valid.cpu().numpy()[:, keep].astype(bool), ref["valid"])
+    _log("evaluate by lanes", len(sizes), K, "ok")
