@@ -57,9 +57,9 @@ def _compare_grads(t, ref, cfg, attention=True, film=True, tol=None):
     assert worst[0] <= tol, worst
 
 
-def _run(cfg, g, w, seed=0, attention=None, film=None):
+def _run(cfg, g, w, seed=0, attention=None, film=None, make=_trainer):
     import torch
-    t = _trainer(cfg, g, w, attention=attention, film=film)
+    t = make(cfg, g, w, attention=attention, film=film)
     logits, _ = t.forward()
     dl = np.random.default_rng(seed).normal(size=(g.n_nodes, cfg.n_devices)) / np.sqrt(g.n_nodes)
     t.backward(torch.from_numpy(dl.astype(np.float32)).cuda())
@@ -234,10 +234,11 @@ def test_directional_derivative_full_size_fp32():
 
 
 # One graph size or head layout a branch of the products' and the attention's
-# dispatch: rows one past a tile, products of many rows with a ragged last tile
-# (d_ff = 1,024: 8 column tiles, so 8,193 rows take the direct-to-register
-# kernel), odd output widths (scalar loads), each head size with one and two
-# columns a lane, memories longer than and unaligned to the segments.
+# dispatch with aligned arrays: rows one past a tile, products of many rows with a
+# ragged last tile (d_ff = 1,024: 8 column tiles, so 8,193 rows take the
+# direct-to-register kernel), an odd number of devices in the head, head sizes of 16
+# and 32 with one and two columns a lane and 64 with one, memories longer than and
+# unaligned to the segments.
 KERNEL_PATHS = [
     ("tile_plus_1_odd_devices", "bf16", dict(graph_sizes=(129,), hidden=128, heads=4, n_devices=7)),
     ("many_rows_ragged", "bf16", dict(graph_sizes=(8193,), hidden=128, heads=4, d_ff=1024, seg_len=512, mem_len=100)),
@@ -256,6 +257,57 @@ def test_backward_parity_kernel_paths(label, dtype, over):
     _log("backward kernel path", label)
     t, ref, att, fl = _run(cfg, g, w, seed=3)
     _compare_grads(t, ref, cfg, att, fl)
+
+
+def _unaligned_trainer(cfg, g, w, **pol):
+    """A Trainer whose features, GNN weights and gradients lie one element past a
+    16-byte boundary, each between guard elements (t.guards)."""
+    import torch
+
+    from paper_1910_01578_amd import gdp
+    t = _trainer(cfg, g, w, **pol)
+    t.guards = []
+
+    def move(a):
+        buf = torch.full((a.numel() + 18,), 7.0, dtype=a.dtype, device=a.device)
+        v = buf[1:a.numel() + 1].view(a.shape)
+        v.copy_(a)
+        assert v.data_ptr() % 16 == a.element_size()
+        t.guards.append((buf, a.numel()))
+        return v
+    t.graph.x = move(t.graph.x)
+    t.graph.c.x = t.graph.x.data_ptr()
+    t.policy.gnn_t = [{k: move(a) for k, a in l.items()} for l in t.policy.gnn_t]
+    t.grad_gnn = [{k: move(a) for k, a in l.items()} for l in t.grad_gnn]
+    t.grad_placer = [{k: move(a) for k, a in l.items()} for l in t.grad_placer]
+    t.grad_head = {k: move(a) for k, a in t.grad_head.items()}
+    order = ("w_pool", "b_pool", "w_self", "w_neigh", "b_upd")
+    for l in range(cfg.gnn_layers):
+        t.policy._gl[l] = gdp.GdpGnnLayer(*[t.policy.gnn_t[l][k].data_ptr() for k in order])
+        t._gg[l] = gdp.GdpGnnLayerGrad(*[t.grad_gnn[l][k].data_ptr() for k in order])
+    for l in range(cfg.placer_layers):
+        t._gp[l] = gdp.GdpPlacerLayerGrad(*[t.grad_placer[l][k].data_ptr() for k in gdp.PLACER_LAYER_FIELDS])
+    t.grads.w_out, t.grads.b_out = t.grad_head["w_out"].data_ptr(), t.grad_head["b_out"].data_ptr()
+    return t
+
+
+@pytest.mark.parametrize("dtype,over", [
+    ("f32", dict(graph_sizes=(65,))),                                 # one piece of k, one past a 64-row tile
+    ("bf16", dict(graph_sizes=(65,))),
+    ("f32", dict(graph_sizes=(700, 1))),                              # two pieces, added by elements
+    ("bf16", dict(graph_sizes=(1030, 3), hidden=128, heads=8, d_ff=512)),
+])
+def test_backward_parity_unaligned_arrays(dtype, over):
+    """The products' scalar loads and stores, which arrays off a 16-byte boundary take
+    (placer weights have to be aligned; the calls accept any other array as it is):
+    one and several pieces of k, bias sums, both types, nothing written beside."""
+    cfg = W.get_config("tiny_layered_256").replace(dtype=dtype, **over)
+    g, w = W.make_graph(cfg), W.make_weights(cfg)
+    _log("backward unaligned", dtype, g.n_nodes)
+    t, ref, att, fl = _run(cfg, g, w, seed=4, make=_unaligned_trainer)
+    _compare_grads(t, ref, cfg, att, fl)
+    for buf, n in t.guards:
+        assert bool((buf[:1] == 7).all()) and bool((buf[n + 1:] == 7).all())
 
 
 def _gradients(t, dl):
