@@ -122,6 +122,47 @@ def test_evaluate_time_range_marks_the_graph(cost):
     assert np.array_equal(got[1], ref["makespan"][1])
 
 
+@pytest.mark.parametrize("xfer", [2 ** 26 - 1, 2 ** 26, 2 ** 31 - 1])
+@pytest.mark.parametrize("v,preds,lanes", [
+    (100, range(90, 98), False),     # in the op's own window of 64, more than its slots hold
+    (100, range(40, 48), False),     # in the window before it, likewise
+    (200, range(10, 18), False),     # further back
+    (200, (10, 17, 130, 150, 190, 191, 192, 193), True),
+])
+def test_evaluate_transfer_range(v, preds, lanes, xfer):
+    """A transfer of 2^26 units and more gives -1 where its edge crosses devices and
+    nowhere else, wherever the predecessor lies; one of 2^26 - 1 is exact.  Sample i
+    has the i-th of eight such predecessors away from op v's device, the last none."""
+    import torch
+
+    from paper_1910_01578_amd import gdp
+    n, D, preds = 256, 4, list(preds)
+    base = W.get_config("tiny_layered_256").replace(graph_sizes=(n,))
+    rows = [[v] if u in preds else [] for u in range(n)]
+    row_ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
+    rng = np.random.default_rng(v)
+    g = W.graph_from_arrays(base, [0, n], row_ptr, np.concatenate(rows).astype(np.int64), W.make_features(base, n, rng))
+    out = rng.integers(0, 90, n).astype(np.int32)
+    out[preds] = xfer
+    costs = W.OpCosts(np.zeros(n, np.int32), out, rng.integers(1, 200, n).astype(np.int32), np.array([10 ** 6], np.int64))
+    kinds = len(preds) + 1
+    pl = np.tile(rng.integers(1, D, n).astype(np.int32), (kinds, 1))
+    pl[:, v] = pl[:, preds] = 0
+    for i, u in enumerate(preds):
+        pl[i, u] = 1 + i % (D - 1)
+    K = 16384 if lanes else kinds                # a lane a sample takes many samples
+    ref = O.simulate_placements(g.graph_ptr, g.row_ptr, g.col_idx, pl, D, costs.op_cost, costs.out_xfer, costs.op_mem,
+                                costs.mem_cap)["makespan"][0]
+    assert np.all(ref[:-1] == xfer) and ref[-1] == 0
+    pl = pl[np.arange(K) % kinds]
+    ev = gdp.Evaluator(gdp.DeviceGraph(g, base.dtype), D, K, costs)
+    mk, _, _ = ev.evaluate(torch.from_numpy(pl).cuda())
+    torch.cuda.synchronize()
+    want = np.where(ref >= 2 ** 26, -1, ref)[np.arange(K) % kinds]
+    assert np.array_equal(mk.cpu().numpy()[0], want)
+    _log("evaluate transfer", v, xfer, "ok")
+
+
 def test_evaluate_feeds_advantages():
     """run_time from gdp_evaluate and its validity go straight into gdp_advantages."""
     import torch
