@@ -277,33 +277,90 @@ __device__ __forceinline__ void for_tiles(char* lds, int tiles, Load load, Work 
   }
 }
 
-// Query q's attention over keys [k0, k1) one key at a time in fp32: m, the sum of
-// 2^(s - m) and the lane's rows 16 db + 4 g4 + r of the weighted values.
+// What the matrix instructions cannot form because an operand is infinite, or rounds
+// to a bf16 infinity, and so has no planes: a result that is not finite is formed
+// again, one row after another in fp32.  Once it is NaN it stays so.
+template <int DH>
+__device__ __forceinline__ float dot_fp32(const float* x, const float* y, float mul) {
+  float t = 0.f;
+  for (int i = 0; i < DH; ++i) t = fmaf(x[i] * mul, y[i], t);
+  return t;
+}
+// The lane's values 16 db + 4 g4 + r: o += w * row.
+template <int DB>
+__device__ __forceinline__ void add_row_fp32(f32x4 (&o)[DB], float w, const float* row, int g4) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    const float4 v = *reinterpret_cast<const float4*>(row + db * 16 + 4 * g4);
+    o[db][0] = fmaf(w, v.x, o[db][0]);
+    o[db][1] = fmaf(w, v.y, o[db][1]);
+    o[db][2] = fmaf(w, v.z, o[db][2]);
+    o[db][3] = fmaf(w, v.w, o[db][3]);
+  }
+}
+template <int DB, int COLS>
+__device__ __forceinline__ bool finite_column(const f32x4 (&o)[DB][COLS], int c) {
+  float any = 0.f;
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) any = fmaf(o[db][c][r], 0.f, any);
+  return any == any;
+}
+// Query q's attention over keys [k0, k1): m, the sum of 2^(s - m) and the weighted values.
 template <int DH>
 __device__ __forceinline__ void attend_fp32(const float* __restrict__ qkv, int ld, int d, int q, int k0, int k1, int c0,
                                             int g4, float mul, float& m, float& sum, f32x4 (&o)[DH / 16]) {
-  auto score = [&](int j) {
-    const float *x = qkv + (size_t)q * ld + c0, *y = qkv + (size_t)j * ld + d + c0;
-    float t = 0.f;
-    for (int i = 0; i < DH; ++i) t = fmaf(x[i] * mul, y[i], t);
-    return t;
-  };
+  auto score = [&](int j) { return dot_fp32<DH>(qkv + (size_t)q * ld + c0, qkv + (size_t)j * ld + d + c0, mul); };
   m = -INFINITY;
   sum = 0.f;
 #pragma unroll
   for (int db = 0; db < DH / 16; ++db) o[db] = zero4();
-  for (int j = k0; j < k1; ++j) m = fmaxf(m, score(j));
-  for (int j = k0; j < k1 && sum == sum; ++j) {            // NaN stays NaN
+  for (int j = k0; j < k1 && sum == sum; ++j) {
+    const float s = score(j);
+    m = fmaxf(m, s);
+    if (s != s) sum = s;
+  }
+  for (int j = k0; j < k1 && sum == sum; ++j) {
     const float p = exp2f(score(j) - m);
     sum += p;
+    add_row_fp32<DH / 16>(o, p, qkv + (size_t)j * ld + 2 * d + c0, g4);
+  }
+}
+// Query q's dQ (less the scale) over keys [k0, k1), from its log-sum-exp L and Dq.
+template <int DH>
+__device__ __forceinline__ void query_grad_fp32(const float* __restrict__ qkv, const float* __restrict__ dO, int ld, int d,
+                                                int q, int k0, int k1, int c0, int g4, float mul, float L, float Dq,
+                                                f32x4 (&dq)[DH / 16]) {
 #pragma unroll
-    for (int db = 0; db < DH / 16; ++db) {
-      const float4 v = *reinterpret_cast<const float4*>(qkv + (size_t)j * ld + 2 * d + c0 + db * 16 + 4 * g4);
-      o[db][0] = fmaf(p, v.x, o[db][0]);
-      o[db][1] = fmaf(p, v.y, o[db][1]);
-      o[db][2] = fmaf(p, v.z, o[db][2]);
-      o[db][3] = fmaf(p, v.w, o[db][3]);
-    }
+  for (int db = 0; db < DH / 16; ++db) dq[db] = zero4();
+  float w = 0.f;
+  for (int j = k0; j < k1 && w == w; ++j) {
+    const float* k = qkv + (size_t)j * ld + d + c0;
+    const float s = dot_fp32<DH>(qkv + (size_t)q * ld + c0, k, mul), dp = dot_fp32<DH>(dO + (size_t)q * d + c0, k + d, 1.0f);
+    w = exp2f(s - L) * (dp - Dq);
+    add_row_fp32<DH / 16>(dq, w, k, g4);
+  }
+}
+// A key's dK (less the scale) and dV from the queries of the segments from seg0
+// that hold it in their band, up to `end`.
+template <int DH>
+__device__ __forceinline__ void key_grad_fp32(const float* __restrict__ qkv, const float* __restrict__ dO,
+                                              const float* __restrict__ Dq, const float* __restrict__ lse, int ld, int d,
+                                              int heads, int head, int key, int seg0, int seg, int mem, int end, int c0,
+                                              int g4, float mul, f32x4 (&dk)[DH / 16], f32x4 (&dv)[DH / 16]) {
+#pragma unroll
+  for (int db = 0; db < DH / 16; ++db) dk[db] = dv[db] = zero4();
+  const float* k = qkv + (size_t)key * ld + d + c0;
+  float w = 0.f;
+  for (int i = seg0; i < end && w == w; ++i) {
+    const int sg0 = seg0 + (i - seg0) / seg * seg;
+    if (sg0 > seg0 && key < sg0 - mem) break;
+    const float *q = qkv + (size_t)i * ld + c0, *g = dO + (size_t)i * d + c0;
+    const float p = exp2f(dot_fp32<DH>(k, q, mul) - lse[(size_t)i * heads + head]);
+    w = p * (dot_fp32<DH>(g, k + d, 1.0f) - Dq[(size_t)i * heads + head]);
+    add_row_fp32<DH / 16>(dv, p, g, g4);
+    add_row_fp32<DH / 16>(dk, w, q, g4);
   }
 }
 
@@ -400,13 +457,7 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const float* __restrict__ qkv,
     lsum[c] += xor_shfl(lsum[c], 16);
     lsum[c] += xor_shfl(lsum[c], 32);
     if (q[c] >= b.r1) continue;
-    // a key or value that is infinite, or rounds to a bf16 infinity, has no planes
-    float any = lsum[c] * 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) any = fmaf(oacc[db][c][r], 0.f, any);
-    if (any != any) {
+    if (!(lsum[c] * 0.f == 0.f) || !finite_column(oacc, c)) {
       f32x4 t[DB];
       attend_fp32<DH>(qkv, ld, d, q[c], k0, k1, c0, g4, scale * kLog2e, m[c], lsum[c], t);
 #pragma unroll
@@ -491,6 +542,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(const float* __restrict__
 #pragma unroll
   for (int c = 0; c < COLS; ++c) {
     if (q[c] >= b.r1) continue;
+    if (!finite_column(dq, c)) {
+      f32x4 t[DB];
+      query_grad_fp32<DH>(qkv, dO, ld, d, q[c], k0, k1, c0, g4, scale * kLog2e, L2[c], Dv[c], t);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) dq[db][c] = t[db];
+    }
 #pragma unroll
     for (int db = 0; db < DB; ++db)
       *reinterpret_cast<float4*>(dqkv + (size_t)q[c] * lddq + c0 + db * 16 + 4 * g4) =
@@ -541,17 +598,17 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
   }
   auto seg_of = [&](int i) { return b.seg0 + (i < own ? 0 : 1 + (i - own) / per) * seg; };
   auto row_of = [&](int i) { return seg_of(i) + (i < own ? i : (i - own) % per) * kAttnTile; };
+  auto store_key = [&](const f32x4& k4, const f32x4& v4, int at, int db, float* out, int ldo, int first) {
+    float* p = out + (size_t)at * ldo + first + c0 + db * 16 + 4 * g4;
+    *reinterpret_cast<float4*>(p) = make_float4(k4[0] * scale, k4[1] * scale, k4[2] * scale, k4[3] * scale);
+    *reinterpret_cast<float4*>(p + d) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+  };
   auto store = [&](float* out, int ldo, int first) {
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
       if (key[c] >= b.r1) continue;
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        float* p = out + (size_t)key[c] * ldo + first + c0 + db * 16 + 4 * g4;
-        *reinterpret_cast<float4*>(p) =
-            make_float4(dk[db][c][0] * scale, dk[db][c][1] * scale, dk[db][c][2] * scale, dk[db][c][3] * scale);
-        *reinterpret_cast<float4*>(p + d) = make_float4(dv[db][c][0], dv[db][c][1], dv[db][c][2], dv[db][c][3]);
-      }
+      for (int db = 0; db < DB; ++db) store_key(dk[db][c], dv[db][c], key[c], db, out, ldo, first);
     }
   };
   // lse (waves 0, 2) and Dq (waves 1, 3) of a tile's queries, one value per lane
@@ -621,6 +678,25 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(const float* __restrict_
       });
   if (tiles == own) store(dqkv_live, ldl, d);
   store(dkv_all, lda, 0);
+  // (a sum that was not finite after the own segment is not now)
+  unsigned again = 0;
+#pragma unroll
+  for (int c = 0; c < COLS; ++c)
+    if (key[c] < b.r1 && !(finite_column(dk, c) && finite_column(dv, c))) again |= 1u << c;
+  for (; again; again &= again - 1) {
+    const int at = b.r0 + (wave * COLS + __builtin_ctz(again)) * 16 + col;
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+      f32x4 tk[DB], tv[DB];
+      key_grad_fp32<DH>(qkv, dO, Dq, lse, ld, d, heads, head, at, b.seg0, seg, mem, part ? end : b.seg1, c0, g4,
+                        scale * kLog2e, tk, tv);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        if (part) store_key(tk[db], tv[db], at, db, dkv_all, lda, 0);
+        else store_key(tk[db], tv[db], at, db, dqkv_live, ldl, d);
+      }
+    }
+  }
 }
 
 // Dq[v][h] = dO[v] . O[v] over the head's columns, one thread per (v, h).

@@ -33,7 +33,8 @@ def _trainer(cfg, g, w, **pol):
 def _tensor_err(got, ref):
     got = np.asarray(got, np.float64)
     ref = np.asarray(ref, np.float64)
-    return float(np.abs(got - ref).max() / max(np.abs(ref).max(), 1e-30))
+    e = float(np.abs(got - ref).max() / max(np.abs(ref).max(), 1e-30))
+    return e if e == e else float("inf")       # (a NaN would lose every comparison of max())
 
 
 def _compare_grads(t, ref, cfg, attention=True, film=True, tol=None):
@@ -372,11 +373,11 @@ def test_attention_rounds_both_ways_alike(heads, seg):
     assert max(got.values()) <= 1.5e-6, got
 
 
-def _extreme(case, dtype, n, hidden):
+def _extreme(case, dtype, n, hidden, **over):
     """A policy and a graph whose products meet operands that a bf16 cannot hold,
     every result of the forward finite."""
-    cfg = W.get_config("tiny_layered_256").replace(dtype=dtype, graph_sizes=(n,), hidden=hidden, heads=hidden // 32,
-                                                   placer_layers=1, film=False)
+    cfg = W.get_config("tiny_layered_256").replace(**{**dict(dtype=dtype, graph_sizes=(n,), hidden=hidden,
+                                                             heads=hidden // 32, placer_layers=1, film=False), **over})
     g, w = W.make_graph(cfg), W.make_weights(cfg)
     x = g.x.copy()
     rows = [0, n // 2, n - 1]
@@ -405,6 +406,25 @@ def _extreme(case, dtype, n, hidden):
         put(w.gnn[0], "w_self", one_large)
         put(w.gnn[1], "w_self", negative(5))
         put(w.gnn[1], "w_pool", negative(5))
+    elif case == "huge_keys":                  # keys of 3.4e38 in column 0 for some rows: no weight, no gradient
+        x[:, 3] = 0.0
+        x[rows, 3] = 1.0                       # the rows' column 5 is 1, the others' 0
+        for layer, col in zip(w.gnn, (3, 5)):
+            def carry(a, col=col):
+                a[5] = 0.0
+                a[5, col] = 1.0
+            put(layer, "w_self", carry)
+            put(layer, "w_neigh", lambda a: a[5].fill(0.0))
+            put(layer, "b_upd", lambda a: a[5:6].fill(0.0))
+
+        def keys(a):
+            a[[0, hidden]] = 0.0
+            a[hidden, 5] = 3.4e38
+
+        def biases(a):
+            a[0], a[hidden] = -1.0, 0.0
+        put(w.placer[0], "w_qkv", keys)
+        put(w.placer[0], "b_qkv", biases)
     else:                                      # keys of minus infinity for part of the rows: no weight
         def keys(a):
             a[0] = 0.0                         # query column 0: -1, from its bias
@@ -452,4 +472,27 @@ def test_operands_beyond_bf16(case, dtype, n, hidden):
             assert np.isnan(to_np(t.grad_gnn[0][k][:, 3])).all()
             ref["gnn"][0][k][:, 3] = 0.0
             t.grad_gnn[0][k][:, 3] = 0.0
+    _compare_grads(t, ref, cfg, film=False)
+
+
+@pytest.mark.parametrize("heads,hidden,seg", [(4, 64, 64), (4, 64, 128), (2, 64, 64), (4, 128, 128), (2, 128, 64)])
+def test_gradients_of_keys_beyond_bf16(heads, hidden, seg):
+    """Finite keys that round to a bf16 infinity, without weight in any query: the
+    gradients of every query and key are those of fp32 products, in each form of
+    the attention's backward (head sizes of 16, 32 and 64, one and two columns)."""
+    import torch
+    n = 300
+    cfg, g, w = _extreme("huge_keys", "f32", n, hidden, heads=heads, seg_len=seg, mem_len=50)
+    _log("keys beyond bf16", heads, hidden, seg)
+    t = _trainer(cfg, g, w)
+    logits, _ = t.forward()
+    dl = (np.random.default_rng(9).normal(size=(n, cfg.n_devices)) / np.sqrt(n)).astype(np.float32)
+    t.backward(torch.from_numpy(dl).cuda())
+    torch.cuda.synchronize()
+    gnn, pl, hd = w.f64()
+    ref = PG.policy_backward(g.graph_ptr, g.row_ptr, g.col_idx, g.x, gnn, pl, hd["w_out"], hd["b_out"],
+                             dl.astype(np.float64), fanout=cfg.fanout, nb_seed=cfg.nb_seed, n_heads=cfg.heads,
+                             seg_len=cfg.seg_len, mem_len=cfg.mem_len, film=False, decisions=t.decisions())
+    assert np.isfinite(ref["logits"]).all()
+    assert rel_err_rows(to_np(logits), ref["logits"]) <= TOL["f32"]
     _compare_grads(t, ref, cfg, film=False)
