@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "host_plan.h"
 #include "kernels.h"
 
 namespace gdp {
@@ -562,16 +563,21 @@ __global__ __launch_bounds__(256) void k_list_schedule(EvalArgs a, GraphTable wt
 
 }  // namespace
 
-// Work-groups per CU follow from the ring in LDS (R words, 14 KB beside it):
-// the longest ring while every (graph, sample) still has a CU of its own, a
-// shorter one (more read-backs, several work-groups per CU) as they multiply,
-// and never longer than the longest graph needs.
+// Work-groups per CU follow from the ring in LDS (R words, kBesideRing bytes
+// beside it): the longest ring with which every (graph, sample) still runs at once
+// (256, 512 and 768 of them), a shorter one (more read-backs) as they multiply, and
+// never longer than the longest graph needs.  What counts is that they run at once.
+// 52,000 ops, rings of 32,768 / 16,384 / 8,192 / 4,096, us: 256 samples 1,174 / 1,130 /
+// 1,131 / 1,111, 512 samples 2,285 / 1,205 / 1,191 / 1,171, 1,024 samples 4,521 / 2,339 /
+// 2,247 / 1,348.  Between the lengths that do, read-backs decide: 40,000 ops of which each
+// reads three up to 12,000 back, 512 samples: 1,641 / 891 / 932 / 992 us.
+constexpr int kBesideRing = 15 * 1024, kLds = 160 * 1024, kCus = 256;
 int eval_ring(const int32_t* graph_ptr, int G, int K) {
   int most = 0;
   for (int g = 0; g < G; ++g) most = std::max(most, graph_ptr[g + 1] - graph_ptr[g]);
   const int64_t groups = (int64_t)G * K;
-  int r = groups <= 256 ? 32768 : groups <= 512 ? 16384 : groups <= 1024 ? 8192 : 4096;
-  while (r > 4096 && r / 2 >= most) r /= 2;
+  int r = 32768;
+  while (r > kEvalMinRing && (r / 2 >= most || groups > (int64_t)kCus * (kLds / (4 * r + kBesideRing)))) r /= 2;
   return r;
 }
 
@@ -606,7 +612,7 @@ hipError_t launch_evaluate(const EvalLaunch& L, hipStream_t s) {
     case 32768: hipLaunchKernelGGL((k_list_schedule<32768>), grid, block, 0, s, a, wt, caps); break;
     case 16384: hipLaunchKernelGGL((k_list_schedule<16384>), grid, block, 0, s, a, wt, caps); break;
     case 8192: hipLaunchKernelGGL((k_list_schedule<8192>), grid, block, 0, s, a, wt, caps); break;
-    default: hipLaunchKernelGGL((k_list_schedule<4096>), grid, block, 0, s, a, wt, caps); break;
+    default: hipLaunchKernelGGL((k_list_schedule<kEvalMinRing>), grid, block, 0, s, a, wt, caps); break;
   }
   return hipGetLastError();
 }

@@ -210,6 +210,8 @@ def _dag(n, rng, dense, far, far_span):
     (33000, 2, 8, 0, 3000, 32700),   # 32,768 finish times on chip: read-backs at their edge
     (17000, 260, 3, 0, 900, 16300),  # 16,384 on chip
     (8300, 515, 2, 0, 900, 8100),    # 8,192
+    (8300, 768, 2, 0, 900, 8100),    # 8,192 for the last time
+    (8300, 769, 2, 0, 900, 8100),    # 4,096 for the first time
     (4200, 1030, 8, 0, 900, 4000),   # 4,096
 ])
 def test_evaluate_windows_and_rings(n, K, D, dense, far, far_span):
