@@ -19,6 +19,8 @@ static_assert(kPoolRows == kMeanpoolRows, "mean-pool chunk size");
 static_assert(kAttnQ == kAttnBlockQ, "attention query block");
 static_assert(kSampleRows == kSampleChunk, "sampling chunk");
 static_assert(kEvalWindowRows == kEvalWindow && kEvalChunkRows == kEvalChunk, "evaluator blocks");
+static_assert(kColSumRows == tr::kColChunkRows, "column-sum chunk");
+static_assert(kMaxTrainPlacerLayers <= kFilmLayersPerLaunch, "the backward's FiLM weights are one launch");
 
 // ---------------------------------------------------------------------------
 // Event timer (diagnostics): an event pair around every launch of a selected
