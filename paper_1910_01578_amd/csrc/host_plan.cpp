@@ -314,7 +314,7 @@ void plan_train(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* pl, Tr
   t->h[0] = 0;
   t->X[0] = t->h[gnn->n_layers];
   for (int l = 0; l < pl->n_layers; ++l) {
-    t->Y[l] = carve_add(&c, N * d * 4);
+    t->Y[l] = pl->film ? carve_add(&c, N * d * 4) : 0;   // without FiLM the layer reads X[l]
     t->QKV[l] = pl->attention ? carve_add(&c, N * 3 * d * 4) : 0;
     t->O[l] = pl->attention ? carve_add(&c, N * d * 4) : 0;
     t->lse_att[l] = pl->attention ? carve_add(&c, N * heads * 4) : 0;

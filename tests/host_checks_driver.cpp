@@ -496,6 +496,14 @@ static void train_paths() {
     ++g_failures;
     printf("FAIL train plan without attention\n");
   }
+  const size_t with_film = tp.store_total;
+  p.film = 0;
+  plan_train(&g, &n, &p, &tp);
+  ++g_checks;
+  if (tp.Y[0] != 0 || tp.store_total + (size_t)p.n_layers * g.n_nodes * p.d_model * 4 > with_film) {
+    ++g_failures;
+    printf("FAIL train plan without FiLM\n");
+  }
 }
 
 // The offset that a lane's vector load forms, row * stride, by a signed 24-bit
