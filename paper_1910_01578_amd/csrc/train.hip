@@ -296,7 +296,6 @@ hipError_t launch_film_bwd(const float* dy, const float* x, int d, const float* 
 // dW_l[c][h] = sum_g dfilm_l[g][c] x0[g][h] and db_l[c] = sum_g dfilm_l[g][c], for
 // gamma's and beta's weights of every layer (blockIdx.y = 2 l + which); a
 // work-group per c.
-template <int>
 __global__ __launch_bounds__(256) void k_film_wgrad(FilmWeightGrads gr, const float* __restrict__ dfilm,
                                                     const float* __restrict__ x0, int G, int d, int H) {
   const int l = blockIdx.y >> 1, c = blockIdx.x;
@@ -349,7 +348,7 @@ __global__ __launch_bounds__(1024) void k_film_dx0(FilmLayers<T> w, int layers, 
 template <typename T>
 hipError_t launch_film_weights_bwd(const FilmLayers<T>& w, const FilmWeightGrads& gr, int layers, const float* dfilm,
                                    const float* x0, int G, int d, int H, float* dx0, hipStream_t s) {
-  hipLaunchKernelGGL((k_film_wgrad<0>), dim3(d, 2 * layers), dim3(256), 0, s, gr, dfilm, x0, G, d, H);
+  hipLaunchKernelGGL(k_film_wgrad, dim3(d, 2 * layers), dim3(256), 0, s, gr, dfilm, x0, G, d, H);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_film_dx0<T>), dim3(H / 64, G), dim3(1024), 0, s, w, layers, dfilm, G, d, H, dx0);

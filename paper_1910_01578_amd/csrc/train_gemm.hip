@@ -450,7 +450,7 @@ __global__ __launch_bounds__(256, 2) void k_linear_split(GemmStrided<float, bf16
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g4 = lane >> 4;
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   const int n0 = (tile % nt) * kLinTile, m0 = (tile / nt) * kLinTile;
-  const int steps = g.K / kLinStep;
+  const int steps = g.K / kLinStep;                      // even (host-checked)
   const bf16* w = g.b + (size_t)n0 * g.sbn;
   auto fetch = [&](int s) {                              // step s's weights (past the end: the last step's again)
     const dma::DmaTile<bf16, kLinTile, kLinStep, 4> t(ring[s % 3], w + min(s, steps - 1) * kLinStep, (int)g.sbn, kLinTile - 1);
@@ -491,7 +491,6 @@ __global__ __launch_bounds__(256, 2) void k_linear_split(GemmStrided<float, bf16
 #pragma unroll
     for (int i = 0; i < 2; ++i) fa[i] = split8(raw[set][i]);
     load(set, s + 2);
-    if (s >= steps) return;                              // one more after an odd number
     const bf16* b = ring[s % 3];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -672,7 +671,7 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
   // CU: k_linear_split.
   if constexpr (std::is_same<TA, float>::value && std::is_same<TB, bf16>::value) {
     const long tiles = (long)((g.M + kLinTile - 1) / kLinTile) * (g.N / kLinTile);
-    if (akf && bkf && vec && g.N % kLinTile == 0 && tiles >= 512) {
+    if (akf && bkf && vec && g.N % kLinTile == 0 && g.K % (2 * kLinStep) == 0 && tiles >= 512) {
       const dim3 grid((unsigned)tiles), block(256);
 #define GDP_LINEAR_CASE(E) \
   case E: hipLaunchKernelGGL((k_linear_split<E>), grid, block, 0, s, g, g.N / kLinTile); return hipGetLastError()
@@ -691,12 +690,16 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
 #define GDP_GEMM_CASE(E, AKF, BKF) \
   case E: e = launch_form<TA, TB, AKF, BKF, E>(g, bm, splits, kps, part, vec, s); break
   if (akf && bkf) {
-    switch (epi) {
+    if constexpr (std::is_same<TA, float>::value) {
+      switch (epi) {
+        GDP_GEMM_CASE(E_BIAS | E_RELU, true, true);
+        GDP_GEMM_CASE(E_BIAS | E_RES, true, true);
+        GDP_GEMM_CASE(E_ACC, true, true);
+      }
+    }
+    switch (epi) {                              // bf16 features too
       GDP_GEMM_CASE(E_BIAS, true, true);
-      GDP_GEMM_CASE(E_BIAS | E_RELU, true, true);
       GDP_GEMM_CASE(E_BIAS | E_SIGMOID, true, true);
-      GDP_GEMM_CASE(E_BIAS | E_RES, true, true);
-      GDP_GEMM_CASE(E_ACC, true, true);
     }
   } else if (akf && g.sbn == 1) {
     if constexpr (std::is_same<TA, float>::value) {
