@@ -2,7 +2,8 @@
 // Section 3.1: the graph embedding network trains jointly with the placement
 // network; Section 3.2: the cached segment memory passes no gradient): the
 // training forward pass that keeps every intermediate, the backward pass and
-// the Adam update.  Everything here computes in fp32 (weights and inputs of
+// the Adam update, but for the dense products (train_gemm.hip) and the attention
+// (train_attn.hip).  Everything here computes in fp32 (weights and inputs of
 // bf16 problems are widened on load), with fixed summation orders, so results
 // are deterministic.
 #include <algorithm>

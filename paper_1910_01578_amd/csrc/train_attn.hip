@@ -5,7 +5,7 @@
 //
 // Every fp32 operand, the probabilities and their gradients included, is the
 // exact sum of three bf16 values; a product of two operands is formed from the
-// six pairs of weight 2^-16 and above (the rest is below 2^-26 of it), as the
+// six pairs of weight 2^-16 and above (the rest is up to 2^-24 of it), as the
 // update step's dense products are.
 //
 // A work-group is 4 waves and one head; it owns 64 COLS queries (forward, dQ)

@@ -5,8 +5,9 @@
 // each), a = a1 + a2 + a3 by repeated round-to-nearest, and the product of two
 // bf16 values is exact in fp32.  With a bf16 B (the weights of a bf16 policy)
 // the three products a1 b + a2 b + a3 b are the whole product; with an fp32 B
-// the six products of weight 2^-16 and above are formed (the three left out are
-// below 2^-26 of |a b| each).  Accumulation is the matrix cores' fp32.  The
+// the six products of weight 2^-16 and above are formed (|a2| is up to 2^-8 of |a|
+// and |a3| up to 2^-17, so of the three left out a2 b3 and a3 b2 are up to 2^-25 of
+// |a b| each, all three 2^-24).  Accumulation is the matrix cores' fp32.  The
 // bf16 instructions do 16 times the work of the fp32 ones per cycle, so three
 // products cost 3/16 and six 3/8 of the fp32 instructions.
 //

@@ -1,6 +1,7 @@
-// Launch interface of the update-step kernels (train.hip): the training
-// forward that keeps every intermediate, the backward pass and Adam, all in
-// fp32 arithmetic.
+// Launch interface of the update-step kernels: the training forward that keeps
+// every intermediate, the backward pass and Adam.  train_gemm.hip (dense products)
+// and train_attn.hip (attention) compute in fp32 accuracy on the bf16 matrix cores,
+// train.hip (everything else) in fp32.
 #pragma once
 
 #include <hip/hip_runtime.h>
