@@ -25,7 +25,7 @@
 // LDS; older ones of graphs longer than R nodes are read back from a global
 // copy.  What bounds it is wave 0's chain of LDS
 // round trips: about 280 cycles a repeat and 7 - 10 repeats plus 900 cycles a
-// window.  52,000 ops, 64 samples: 1.01 ms (op by op on one wave: 30.4 ms);
+// window.  52,000 ops, 64 samples: 1.12 ms a call (op by op on one wave: 30.4 ms);
 // 2,500 ops, 16 samples: 77 us (933 us).
 //
 // Times below 2^26 units (they share a word with the device or a lane number),

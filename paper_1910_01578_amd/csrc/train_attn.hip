@@ -23,8 +23,8 @@
 //
 // What bounds it: the vector ALU (exponentials, splits) and the matrix
 // instructions together.  52,000 rows, 8 heads of 32, segments and memory of 512
-// (16x16x4 fp32 instructions before): forward 597 -> 305 us, dQ 853 -> 373 us,
-// dK and dV 1,554 -> 580 us.
+// (16x16x4 fp32 instructions before): forward 597 -> 315 us, dQ 853 -> 409 us,
+// dK and dV 1,554 -> 657 us.
 //
 // The gradients of W_q and W_k are small differences of large sums (a row's ds
 // add up to zero), so what the forward divides by and sums has to agree with what

@@ -36,8 +36,9 @@
 // instructions of a step are about equal (600 - 800 cycles each), and two
 // work-groups a CU overlap them in part.  At 52,000 rows, 16x16x4 fp32
 // instructions before and this kernel now: weight gradient (256 x 1024) 332 ->
-// 153 us, x W^T (1024 x 256, ReLU) now 118 us (230 TFLOP/s); relative error
-// against float64 2.9e-7 -> 1.6e-7 (k = 256), 5.6e-7 -> 2.4e-7 (weight gradient).
+// 143 us, input gradient (1,024 columns, bf16 weights, ReLU') now 181 us (151
+// TFLOP/s); relative error against float64 2.9e-7 -> 8.9e-8 (k = 256), 5.6e-7 ->
+// 2.4e-7 (weight gradient).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -168,8 +169,9 @@ int epi_of(const GemmStrided<TA, TB>& g) {
 // What the epilogue reads for N consecutive columns from (m, n).  A kernel reads
 // it for all of its results before it stores the first: the stores may alias
 // these arrays, so a load behind a store cannot start early, and each of a lane's
-// 16 results would take a memory round trip of its own (52,000 rows: ReLU' mask of
-// 1,024 columns 172 -> 157 us, bias and ReLU 143 -> 137 us).
+// 16 results would take a memory round trip of its own (52,000 rows, both with all
+// planes on one sum: ReLU' mask of 1,024 columns 172 -> 157 us, bias and ReLU 143 ->
+// 137 us).
 template <int EPI, int N>
 struct EpiIn {
   float bias[N];
@@ -437,11 +439,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(GemmStrided<TA, TB> g, in
 // rows go from memory straight to its registers in fragment layout (eight
 // consecutive k a lane), two steps ahead, and are split there; only the weights
 // pass through LDS, by direct loads into a ring of three buffers, two steps
-// ahead.  So LDS moves 40 KB a step instead of 96 and the registers hold the
-// small products' sums apart: 52,000 x 1,024 by 256 in 125 us as in the kernel
-// above (118 - 124 us), with half its error (k = 256: 8.6e-8 against 1.6e-7, k =
-// 1,024: 1.8e-7 against 3.4e-7).  The error is why it is used: a ReLU that falls
-// the other way moves a gradient by a whole term.
+// ahead.  So LDS moves 40 KB a step of 32 instead of 96.  In the kernel above and
+// here, 52,000 rows, us: 256 to 1,024 columns 126 -> 121 (ReLU), 1,024 to 256 131 -> 121
+// (residual), 256 to 768 84 -> 80; 16,384 rows of 128 to 512 16.4 -> 15.5; the same error
+// (8.9e-8 at k = 256, 1.9e-7 at k = 1,024).
 // ---------------------------------------------------------------------------
 constexpr int kLinTile = 128, kLinStep = 32;
 
@@ -641,7 +642,10 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
   if (!akf) vec = vec && g.M % 2 == 0;          // row pairs
   int bm = 64, splits = 1;
   if (akf) {
-    // 128 x 128 tiles when they give at least two work-groups per CU, else 64 x 64
+    // 128 x 128 tiles when they give at least two work-groups per CU, else 64 x 64.
+    // 64 / 128, 256 to 256 columns, us, at 256, 512 and 768 tiles of 128: x W^T 13.6 /
+    // 15.0, 23.0 / 22.2, 32.2 / 30.5, with fp32 weights 19.9 / 19.9, 34.2 / 30.8, 48.5 /
+    // 43.2; dY W 18.9 / 16.5, 30.8 / 24.6, 43.0 / 34.4 (its line would be 256).
     const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
     if (vec && tiles128 >= 512) bm = 128;
   } else {
@@ -649,6 +653,9 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
     // kMostRows rows, each summed in fp32, the pieces added in double; as many as
     // make rounds of two work-groups per CU cheapest (at 52,000 rows a step of
     // 16 takes 1.4 us with the chip full; the pieces' sums cost their traffic).
+    // With 1,000 - 52,000 rows and 64 x 64 to 256 x 1,024 gradients the number chosen
+    // is within 1 % of the best of ten (29,000 rows, 128 x 512: 61 us, one tenth as
+    // many pieces 689 us).
     constexpr int kMostRows = 2048, kLeastRows = 256;
     if (vec && g.M >= 128 && g.N >= 128) bm = 128;
     const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bm - 1) / bm);
@@ -669,7 +676,7 @@ hipError_t launch_gemm_strided(const GemmStrided<TA, TB>& g, float* partial, siz
   float* part = splits > 1 ? partial : nullptr;
   const int epi = epi_of(g);
   // Many rows by bf16 weights, where its 128 x 128 tiles give two work-groups per
-  // CU: k_linear_split.
+  // CU: k_linear_split (as above: 13.0, 20.5 and 29.2 us).
   if constexpr (std::is_same<TA, float>::value && std::is_same<TB, bf16>::value) {
     const long tiles = (long)((g.M + kLinTile - 1) / kLinTile) * (g.N / kLinTile);
     if (akf && bkf && vec && g.N % kLinTile == 0 && g.K % (2 * kLinStep) == 0 && tiles >= 512) {
