@@ -369,7 +369,7 @@ static int place_impl(const gdp_graph* g, const T* node_emb, const float* graph_
   }
 
   GraphTable qt = make_table(g);
-  const int qblocks = prefix_blocks_attention(g->graph_ptr_h, G, p->seg_len, kAttnQ, qt.blk);
+  const int qblocks = prefix_blocks_attention(g->graph_ptr_h, G, segment_len(g, p), kAttnQ, qt.blk);
   const float q_scale = attn_q_scale(d / p->n_heads);
   // The head runs inside the last layer's kernel when D is small enough.
   const bool fused_head = p->n_devices <= kFusedHeadDevices;
@@ -384,7 +384,7 @@ static int place_impl(const gdp_graph* g, const T* node_emb, const float* graph_
     return a;
   };
   auto attn_args = [&](const T* qkv_in, int qb0, int nqb) {
-    AttnArgs<T> a = {qkv_in, 3 * d, o, d, d, p->n_heads, p->seg_len, p->mem_len, nqb};
+    AttnArgs<T> a = {qkv_in, 3 * d, o, d, d, p->n_heads, segment_len(g, p), p->mem_len, nqb};
     a.qblock0 = qb0;
     return a;
   };
@@ -1033,7 +1033,7 @@ int train_forward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer*
       GDP_LAUNCH(GDP_K_TRAIN_FWD, lin<float, T>(Y, d, static_cast<const T*>(Ly.w_qkv), d,
                                                 static_cast<const T*>(Ly.b_qkv), N, 3 * d, d, qkv, 3 * d, tr::ACT_NONE,
                                                 false, cx));
-      GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_attn_fwd(qkv, N, d, p->n_heads, p->seg_len, p->mem_len, gt, O,
+      GDP_LAUNCH(GDP_K_TRAIN_FWD, tr::launch_attn_fwd(qkv, N, d, p->n_heads, segment_len(g, p), p->mem_len, gt, O,
                                                       S(tp.lse_att[l]), st));
       GDP_LAUNCH(GDP_K_TRAIN_FWD, lin<float, T>(O, d, static_cast<const T*>(Ly.w_o), d, static_cast<const T*>(Ly.b_o),
                                                 N, d, d, R1, d, tr::ACT_NONE, false, cx, Y));
@@ -1111,7 +1111,7 @@ int backward_impl(const gdp_graph* g, const gdp_gnn* gnn, const gdp_placer* p, c
                                            cx));
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dR, d, O, d, d, d, N, Gl.w_o, d, Gl.b_o, cx));
       // attention: dK, dV of the own segment (live) and with the memory's part (all)
-      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_attn_bwd(qkv, O, dX, S(tp.lse_att[l]), N, d, p->n_heads, p->seg_len,
+      GDP_LAUNCH(GDP_K_BACKWARD, tr::launch_attn_bwd(qkv, O, dX, S(tp.lse_att[l]), N, d, p->n_heads, segment_len(g, p),
                                                      p->mem_len, gt, W(tp.Dq), dqkv, dkva, st));
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dqkv, 3 * d, Y, d, d, d, N, Gl.w_qkv, d, Gl.b_qkv, cx));
       GDP_LAUNCH(GDP_K_BACKWARD, lin_dw<float>(dkva, 2 * d, Y, d, 2 * d, d, N, Gl.w_qkv + (size_t)d * d, d,

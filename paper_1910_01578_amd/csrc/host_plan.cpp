@@ -156,6 +156,11 @@ int blocks_below(const int32_t* gp, int G, int rows, int R, int* started) {
   return n;
 }
 
+int segment_len(const gdp_graph* g, const gdp_placer* p) {
+  constexpr int kMost = 1 << 30;
+  return g->n_nodes <= kMost && p->seg_len > kMost ? kMost : p->seg_len;
+}
+
 int prefix_blocks_attention(const int32_t* gp, int G, int seg_len, int bq, int32_t* blk) {
   const int qbs = (seg_len + bq - 1) / bq;
   blk[0] = 0;
@@ -228,14 +233,14 @@ void plan_place(const gdp_graph* g, const gdp_placer* pl, PlacePlan* p) {
     p->y1 = p->qkv = p->qkv2 = p->o = p->y0;
     return;
   }
-  p->qblocks = prefix_blocks_attention(g->graph_ptr_h, g->n_graphs, pl->seg_len, kAttnQ, blk);
+  p->qblocks = prefix_blocks_attention(g->graph_ptr_h, g->n_graphs, segment_len(g, pl), kAttnQ, blk);
   p->y1 = carve_add(&p->c, N * d * 4);
   p->qkv = carve_add(&p->c, N * 3 * d * es);
   p->o = carve_add(&p->c, N * d * es);
   // Two parts only where part B still fills a round of its own (and a
   // layer is long enough that the overlap outweighs the extra launches).
   if (N >= (size_t)kSplitRows + kSplitRows / 4)
-    p->split = segment_split(g->graph_ptr_h, g->n_graphs, pl->seg_len, kAttnQ, kSplitRows, &p->split_qblocks);
+    p->split = segment_split(g->graph_ptr_h, g->n_graphs, segment_len(g, pl), kAttnQ, kSplitRows, &p->split_qblocks);
   p->qkv2 = p->split > 0 ? carve_add(&p->c, N * 3 * d * es) : p->qkv;
 }
 

@@ -30,6 +30,9 @@ struct Carve {
 void carve_init(Carve* c);
 size_t carve_add(Carve* c, size_t bytes);   // returns the offset of the new region
 
+// The placer's seg_len, less where a longer one makes no difference and sums with a
+// row number would pass 32 bits.
+int segment_len(const gdp_graph* g, const gdp_placer* p);
 // Per-graph block counts -> prefix (blk[0] = 0 .. blk[G] = total).
 int prefix_blocks_rows(const int32_t* graph_ptr, int G, int rows_per_block, int32_t* blk);
 int prefix_blocks_attention(const int32_t* graph_ptr, int G, int seg_len, int block_q, int32_t* blk);

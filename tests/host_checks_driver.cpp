@@ -534,6 +534,25 @@ static void vec_stride_paths() {
   }
 }
 
+// Segment lengths up to the largest int: one segment a graph.
+static void long_segment_paths() {
+  const gdp_graph g = good_graph();
+  gdp_placer p = good_placer();
+  for (int len : {16, 1 << 30, (1 << 30) + 1, INT32_MAX - 63, INT32_MAX}) {
+    p.seg_len = len;
+    PlacePlan pl;
+    plan_place(&g, &p, &pl);
+    int32_t blk[GDP_MAX_GRAPHS + 1];
+    const int seg = segment_len(&g, &p), blocks = prefix_blocks_attention(g.graph_ptr_h, g.n_graphs, seg, 64, blk);
+    ++g_checks;
+    if (pl.qblocks != g.n_graphs || blocks != g.n_graphs || seg < g.n_nodes ||
+        (int64_t)g.n_nodes + seg > INT32_MAX) {
+      ++g_failures;
+      printf("FAIL segments of %d: %d query blocks\n", len, pl.qblocks);
+    }
+  }
+}
+
 // gdp_evaluate's choice between a lane and a work-group a sample, and that a
 // workspace for K samples serves every smaller K on either side of it.
 static void eval_route_paths() {
@@ -606,6 +625,7 @@ int main() {
   blocks_below_paths();
   train_paths();
   vec_stride_paths();
+  long_segment_paths();
   eval_route_paths();
   error_text();
   printf("%d checks, %d failures\n", g_checks, g_failures);

@@ -496,3 +496,28 @@ def test_gradients_of_keys_beyond_bf16(heads, hidden, seg):
     assert np.isfinite(ref["logits"]).all()
     assert rel_err_rows(to_np(logits), ref["logits"]) <= TOL["f32"]
     _compare_grads(t, ref, cfg, film=False)
+
+
+@pytest.mark.parametrize("seg,mem", [(2 ** 31 - 1, 0), (2 ** 31 - 64, 2 ** 31 - 1), (2 ** 30 + 1, 7)])
+def test_segments_longer_than_any_graph(seg, mem):
+    """Up to the largest int: the same bits as segments that just hold every graph,
+    in the placement network and in both passes of the update step."""
+    import torch
+
+    from paper_1910_01578_amd import gdp
+    dl, got = None, []
+    for s in (640, seg):
+        cfg = W.get_config("tiny_layered_256").replace(graph_sizes=(300, 129), seg_len=s, mem_len=mem)
+        g, w = W.make_graph(cfg), W.make_weights(cfg)
+        t = _trainer(cfg, g, w)
+        logits, _ = t.forward()
+        dl = dl if dl is not None else torch.randn(g.n_nodes, cfg.n_devices, device="cuda")
+        out = {"logits": to_np(logits), **_gradients(t, dl.cpu().numpy())}
+        r = gdp.Runner(t.graph, t.policy, cfg.k_samples)
+        r.forward(cfg.sample_seed)
+        out["place"] = to_np(r.logits)
+        got.append(out)
+    torch.cuda.synchronize()
+    _log("long segments", seg, mem)
+    assert all(np.array_equal(got[0][k], got[1][k]) for k in got[0])
+    assert all(np.isfinite(v).all() for v in got[0].values())
