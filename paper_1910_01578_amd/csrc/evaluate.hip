@@ -26,7 +26,9 @@
 // copy.  What bounds it is wave 0's chain of LDS
 // round trips: about 280 cycles a repeat and 7 - 10 repeats plus 900 cycles a
 // window.  52,000 ops, 64 samples: 1.12 ms a call (op by op on one wave: 30.4 ms);
-// 2,500 ops, 16 samples: 77 us (933 us).
+// 2,500 ops, 16 samples: 77 us (933 us).  Edges beyond the four slots of a node are
+// read from memory again in each round over them; 20,000 ops, 64 samples, op by op
+// before: 3 predecessors each 0.61 ms (14.1), 8 1.9 ms (33.6), 99 21.7 ms (400).
 //
 // Times below 2^26 units (they share a word with the device or a lane number),
 // saturating; a graph with a finish time of 2^26 or more gets the result -1.
